@@ -499,9 +499,9 @@ __global__ __launch_bounds__(1024) void k_coef_bwd(A arg, uint32_t l_from_top) {
       if (b0 + tid <= b_end && mb[b0 + tid]) atomicMin(&next, b0 + tid);
       __syncthreads();
       found = next;
+      __syncthreads();  // every wave has read this step's minimum before another one lowers or clears it
       if (found != kNoRow) break;
     }
-    __syncthreads();
     if (tid == 0) next = kNoRow;
     __syncthreads();
     if (found != kNoRow) {
