@@ -62,13 +62,17 @@ struct CoefQuery {
   uint64_t* l_y;
   uint64_t lstride;
   uint32_t carried;      // bit y: the level with index y has long runs (carries in a launch of their own)
+  uint32_t far;          // bit y: a destination of that level may span very many runs (carries from prefix sums)
   uint32_t iters, it0;   // rows by iteration: values per row (0: coefficient rows), iteration of the first
   const uint64_t* z1;    // rows of single vertices: z, or by iteration z^L [n][iters]
   uint32_t z1_stride;
   uint64_t *P, *Q;  // rows of the level below, prefix rows of this level
   uint64_t* tail;        // [runs][C(k, l-1)] XOR of each run's open part
-  uint64_t* carry;       // [runs][C(k, l-1)] XOR of its segment in the runs before it (long runs)
+  uint64_t* carry;       // [runs][C(k, l-1)] XOR of its segment in the runs before it (long runs), or of all tails
+                         // before it (far runs)
   uint32_t* open_end;    // [runs] end of the entries before its first segment start (long runs)
+  uint64_t* group;       // [runs / 64][C(k, l-1)] sums of 64 tails (far runs)
+  uint32_t* seg;         // [runs] the run in which the segment that it continues starts (far runs)
   uint8_t* started;      // [runs] whether a segment starts in the run
   uint64_t* T;           // [m] per-edge sums (fine-grained queries)
 };

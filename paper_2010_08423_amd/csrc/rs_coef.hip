@@ -1047,9 +1047,87 @@ __device__ __forceinline__ uint32_t open_part(const uint8_t* restart, uint32_t p
   }
 }
 
+// Levels where one destination may span very many runs (see far_levels): summed
+// tail by tail the carries' work grows as the square of the runs of one segment
+// (70 % of 10^6 edges at one vertex, k = 3: row products of 1696 us). There the
+// carry of a run is the exclusive prefix sum of the tails at the run less the
+// one at its segment's first run, two rows whatever the distance. k_coef_fold
+// sums the tails of 64 runs, k_coef_prefix adds up the groups before its own and
+// leaves the prefix sums in carry and each run's segment start in seg. A block
+// takes 64 runs and 64 coefficients, a wave four runs; bound by latency. (One
+// launch whose blocks summed every tail before theirs took 29 to 36 us for 4096 to
+// 10000 runs.)
+template <class A>
+__global__ __launch_bounds__(1024) void k_coef_fold(A arg, uint32_t l) {
+  __shared__ uint64_t part[16][kLanes];
+  const CoefQuery Q = arg.get(blockIdx.z);
+  if (l >= Q.k || !((Q.far >> (l - 2)) & 1u)) return;
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t C = row_width(Q, l), co = blockIdx.y * kLanes + lane, r0 = blockIdx.x * 64 + wv * 4;
+  const Runs R = level_runs(Q, l, arg.waves(blockIdx.z, l));
+  if (blockIdx.y * kLanes >= C || blockIdx.x * 64 >= R.runs) return;
+  uint64_t s = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) s ^= co < C && r0 + i < R.runs ? Q.tail[(uint64_t)(r0 + i) * C + co] : 0;
+  part[wv][lane] = s;
+  __syncthreads();
+  if (wv || co >= C) return;
+#pragma unroll
+  for (uint32_t i = 1; i < 16; ++i) s ^= part[i][lane];
+  Q.group[(uint64_t)blockIdx.x * C + co] = s;
+}
+template <class A>
+__global__ __launch_bounds__(1024) void k_coef_prefix(A arg, uint32_t l) {
+  __shared__ uint64_t before[16][kLanes], part[16][kLanes];
+  __shared__ uint32_t last;
+  const CoefQuery Q = arg.get(blockIdx.z);
+  if (l >= Q.k || !((Q.far >> (l - 2)) & 1u)) return;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6, g = blockIdx.x;
+  const uint32_t C = row_width(Q, l), co = blockIdx.y * kLanes + lane, r0 = g * 64 + wv * 4;
+  const Runs R = level_runs(Q, l, arg.waves(blockIdx.z, l));
+  if (blockIdx.y * kLanes >= C || g * 64 >= R.runs) return;
+  const bool active = co < C;
+  uint64_t row[4], b = 0, s = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) row[i] = active && r0 + i < R.runs ? Q.tail[(uint64_t)(r0 + i) * C + co] : 0;
+  if (active)
+    for (uint32_t i = wv; i < g; i += 64) {  // four in flight
+      uint64_t v[4];
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) v[j] = *(gu64*)(Q.group + (uint64_t)min(i + 16 * j, g - 1) * C + co);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) b ^= i + 16 * j < g ? v[j] : 0;
+    }
+  if (tid == 0) last = 0;
+  before[wv][lane] = b;
+  part[wv][lane] = row[0] ^ row[1] ^ row[2] ^ row[3];
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < 16; ++i) s ^= before[i][lane] ^ (i < wv ? part[i][lane] : 0);
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    if (active && r0 + i < R.runs) Q.carry[(uint64_t)(r0 + i) * C + co] = s;
+    s ^= row[i];
+  }
+  if (blockIdx.y) return;
+  uint32_t m = 0;  // one past the last run before the group in which a segment starts
+  for (uint32_t i = tid; i < g * 8; i += 1024) {  // eight flags per word
+    const uint64_t f = ((const uint64_t*)Q.started)[i];
+    if (f) m = i * 8 + 8 - (uint32_t)__builtin_clzll(f) / 8;
+  }
+  if (m) atomicMax(&last, m);
+  __syncthreads();
+  if (wv == 0) {
+    const uint32_t r = g * 64 + lane;
+    const uint64_t f = __ballot(r < R.runs && Q.started[min(r, R.runs - 1)]) & ((1ull << lane) - 1);
+    if (r < R.runs) Q.seg[r] = f ? g * 64 + 63 - (uint32_t)__builtin_clzll(f) : max(last, 1u) - 1;
+  }
+}
+
 // Carries of a level whose runs are long (see run_coef): per run that continues
 // a segment, the XOR of the tails back to the run the segment starts in, and
-// the end of the rows that lack it.
+// the end of the rows that lack it. On a far level the prefix sums are in carry
+// and nothing reads the tails any more: the carries take their place.
 template <class A>
 __global__ __launch_bounds__(256) void k_coef_carry(A arg, uint32_t l) {
   const CoefQuery Q = arg.get(blockIdx.z);
@@ -1066,12 +1144,21 @@ __global__ __launch_bounds__(256) void k_coef_carry(A arg, uint32_t l) {
                                 min(R.tile(run + 1) * kTile, R.n), lane);
   if (blockIdx.y == 0 && lane == 0) Q.open_end[run] = oe;
   if (oe == p) return;
+  if ((Q.far >> (l - 2)) & 1u) {
+    const uint32_t first = as_const(Q.seg)[run];
+    if (co < C) Q.tail[(uint64_t)run * C + co] = Q.carry[(uint64_t)run * C + co] ^ Q.carry[(uint64_t)first * C + co];
+    return;
+  }
   const uint32_t first = segment_run(Q.started, run, lane);  // (a ballot of all lanes)
   if (co >= C) return;
   uint64_t s = 0;
 #pragma unroll 8
   for (uint32_t r = first; r < run; ++r) s ^= *(gu64*)(Q.tail + (uint64_t)r * C + co);
   Q.carry[(uint64_t)run * C + co] = s;
+}
+// Where k_coef_carry leaves a level's carries.
+__device__ __forceinline__ const uint64_t* carries(const CoefQuery& Q, uint32_t l) {
+  return (Q.far >> (l - 2)) & 1u ? Q.tail : Q.carry;
 }
 
 // One row P_l[p] = z_{dst} Q_l[p] by a wave. Lanes take (label, subset) pairs, so
@@ -1160,6 +1247,7 @@ __global__ __launch_bounds__(256) void k_coef_mul(A arg, uint32_t l, uint32_t wa
   const uint8_t* store = Q.store + y * flag_stride(Q.words);
   if constexpr (CARRIED) {
     const uint32_t units = (R.n + 3) / 4, waves = gridDim.x * 4;
+    const uint64_t* carry = carries(Q, l);
     for (uint32_t u = blockIdx.x * 4 + wv; u < units; u += waves) {
       uint32_t flags = as_const((const uint32_t*)store)[u];
       if (!flags) continue;
@@ -1167,15 +1255,22 @@ __global__ __launch_bounds__(256) void k_coef_mul(A arg, uint32_t l, uint32_t wa
       while (flags) {
         const uint32_t p = u * 4 + (uint32_t)__builtin_ctz(flags) / 8;
         flags &= flags - 1;
-        M.row(arg, Q, p, as_const(dsts)[p], nullptr, p < oe ? Q.carry + (uint64_t)run * M.c_in : nullptr);
+        M.row(arg, Q, p, as_const(dsts)[p], nullptr, p < oe ? carry + (uint64_t)run * M.c_in : nullptr);
       }
     }
   } else {
     uint64_t* carry = dyn_lds + 4 * (wave_lds / 8);
+    const bool far = (Q.far >> (l - 2)) & 1u;
     for (uint32_t run = blockIdx.x; run < R.runs; run += gridDim.x) {
       const uint32_t p_begin = R.tile(run) * kTile, p_end = min(R.tile(run + 1) * kTile, R.n);
       const uint32_t oe = open_part(Q.restart + y * flag_stride(Q.words), p_begin, p_end, lane);
-      if (oe > p_begin) {
+      if (oe > p_begin && far) {
+        const uint32_t first = as_const(Q.seg)[run];
+        __syncthreads();  // the block's last run is done with the carry
+        for (uint32_t i = threadIdx.x; i < M.c_in; i += 256)
+          carry[i] = *(gu64*)(Q.carry + (uint64_t)run * M.c_in + i) ^ *(gu64*)(Q.carry + (uint64_t)first * M.c_in + i);
+        __syncthreads();
+      } else if (oe > p_begin) {
         const uint32_t first = segment_run(Q.started, run, lane);
         __syncthreads();  // the block's last run is done with the carry
         for (uint32_t i = threadIdx.x; i < M.c_in; i += 256) carry[i] = 0;
@@ -1392,6 +1487,7 @@ __global__ __launch_bounds__(256) void k_iter_mul(OneCoef a, uint32_t l) {
   const uint32_t base = lds_addr(tab);
   uint32_t cur = kNoRow;
   const uint32_t units = (R.n + 3) / 4, waves = gridDim.x * 4;
+  const uint64_t* carry = carries(Q, l);
   for (uint32_t u = blockIdx.x * 4 + wv; u < units; u += waves) {
     uint32_t flags = as_const((const uint32_t*)store)[u];
     if (!flags) continue;
@@ -1400,7 +1496,7 @@ __global__ __launch_bounds__(256) void k_iter_mul(OneCoef a, uint32_t l) {
       const uint32_t p = u * 4 + (uint32_t)__builtin_ctz(flags) / 8;
       flags &= flags - 1;
       uint64_t v = *(gu64*)(Q.Q + (uint64_t)p * C + ca);
-      if (p < oe) v ^= *(gu64*)(Q.carry + (uint64_t)run * C + ca);
+      if (p < oe) v ^= *(gu64*)(carry + (uint64_t)run * C + ca);
       const uint32_t dst = as_const(dsts)[p];
       if (dst != cur) {
         cur = dst;
@@ -1510,6 +1606,9 @@ constexpr uint32_t kMulBlocks = 2048;
 constexpr uint64_t kWideSets = 600000;
 // Entries per run from which the carries get a launch of their own.
 constexpr uint64_t kLongRun = 32;
+// Runs that one destination may span from which the carries come from prefix
+// sums: two short launches more against a sum over the square of the runs.
+constexpr uint64_t kFarRuns = 1024;
 
 // Device buffers of one query carved from one region, each 256-byte aligned.
 struct Carver {
@@ -1566,7 +1665,8 @@ static void fill_query(CoefQuery& q, CoefShades& sh, const GraphDev& G, const Qu
 static uint64_t carve_setup(CoefQuery& q, const CoefShades& sh, uint8_t* base) {
   Carver c{base};
   const uint64_t L = q.k - 1, fw = (uint64_t)q.words + q.words / 64;
-  uint64_t tails = 0;
+  uint64_t tails = 0, width = q.iters;
+  for (uint32_t l = 2; l < q.k; ++l) width = std::max<uint64_t>(width, width_in(q, l));
   for (uint32_t l = 2; l < q.k; ++l)
     tails = std::max<uint64_t>(tails, (uint64_t)scan_runs(q, sh, q.m, l) * width_in(q, l));
   // (rows by iteration may be made narrower later, and the last level leaves its sums here)
@@ -1590,6 +1690,8 @@ static uint64_t carve_setup(CoefQuery& q, const CoefShades& sh, uint8_t* base) {
   c.take(q.carry, tails);
   c.take(q.started, 4 * kScanWaves);
   c.take(q.open_end, 4 * kScanWaves);
+  c.take(q.seg, 4 * kScanWaves);
+  c.take(q.group, tails / 64 + width);
   return c.off;
 }
 
@@ -1607,10 +1709,28 @@ static uint32_t carried_levels(const CoefQuery& q, const CoefShades& sh, const u
     if (cnt[l - 2] > kLongRun * scan_runs(q, sh, cnt[l - 2], l)) b |= 1u << (l - 2);
   return b;
 }
+// Levels where one destination may span more than kFarRuns runs. A list with
+// known size is taken to hold a vertex's arrivals at up to eight times the rate at
+// which it holds all edges; sizes that are only bounds (sized false) leave a run's
+// length open, and it is taken as one tile. (40000 of 50000 edges into one vertex,
+// k = 3: 308 us per query with the tails summed one by one, 98 with prefix sums;
+// 700000 of 10^6: 1846 and 214. A 4*10^6-edge motif query, 84000 arrivals at one
+// vertex, few of them in the lists: 1484 and 1527.)
+static uint32_t far_levels(const CoefQuery& q, const CoefShades& sh, const uint32_t* cnt, bool sized, uint64_t m,
+                           uint64_t most_arrivals) {
+  uint32_t b = 0;
+  for (uint32_t l = 2; l < q.k; ++l) {
+    const uint64_t n = cnt[l - 2], runs = scan_runs(q, sh, n, l);
+    const uint64_t span = sized ? std::min({n, most_arrivals, 8 * most_arrivals * n / m + 1}) * runs / std::max<uint64_t>(n, 1)
+                                : most_arrivals / kTile;
+    if (std::min(runs, span) > kFarRuns) b |= 1u << (l - 2);
+  }
+  return b;
+}
 
 // Grid sizes of the launches over one or more queries: the largest any needs.
 struct CoefGrid {
-  uint32_t queries = 0, begin = 1, blocks = 1, k_max = 0, fwd_max = 0, fwd_min = 16, carried = 0;
+  uint32_t queries = 0, begin = 1, blocks = 1, k_max = 0, fwd_max = 0, fwd_min = 16, carried = 0, far = 0;
   bool wide = false, small = true;
   uint32_t runs[kCoefMaxK] = {}, waves[kCoefMaxK] = {}, cblocks[kCoefMaxK] = {}, mul[kCoefMaxK] = {}, carry_mul[kCoefMaxK] = {},
            lds[kCoefMaxK] = {}, carry_lds[kCoefMaxK] = {}, top = 1, per_wave = 64;
@@ -1629,6 +1749,7 @@ struct CoefGrid {
   void levels(const CoefQuery& q, const CoefShades& sh, const uint32_t* cnt) {
     const uint32_t k = q.k;
     carried |= q.carried;
+    far |= q.far;
     for (uint32_t l = 2; l < k; ++l) {
       const uint64_t n = cnt[l - 2];
       const uint32_t r = scan_runs(q, sh, n, l), wl = q.iters ? 0 : mul_lds(k, binom(k, l - 1), binom(k, l));
@@ -1683,6 +1804,10 @@ template <class A>
 static hipError_t launch_coef_level(const A& a, const CoefGrid& g, uint32_t l, hipStream_t st) {
   const uint32_t i = l - 1, nq = g.queries;
   hipLaunchKernelGGL(k_coef_scan<A>, dim3((g.waves[i] + 3) / 4, g.cblocks[i], nq), dim3(256), 0, st, a, l);
+  if ((g.far >> (l - 2)) & 1u) {
+    hipLaunchKernelGGL(k_coef_fold<A>, dim3((g.runs[i] + 63) / 64, g.cblocks[i], nq), dim3(1024), 0, st, a, l);
+    hipLaunchKernelGGL(k_coef_prefix<A>, dim3((g.runs[i] + 63) / 64, g.cblocks[i], nq), dim3(1024), 0, st, a, l);
+  }
   if (g.carry_mul[i]) {
     hipLaunchKernelGGL(k_coef_carry<A>, dim3((g.runs[i] + 3) / 4, g.cblocks[i], nq), dim3(256), 0, st, a, l);
     hipLaunchKernelGGL((k_coef_mul<A, true>), dim3(g.carry_mul[i], 1, nq), dim3(256), 4 * g.carry_lds[i], st, a, l,
@@ -1696,6 +1821,10 @@ static hipError_t launch_coef_level(const A& a, const CoefGrid& g, uint32_t l, h
 static hipError_t launch_iter_level(const OneCoef& a, const CoefGrid& g, uint32_t l, hipStream_t st) {
   const uint32_t i = l - 1, cb = g.cblocks[i];
   hipLaunchKernelGGL(k_coef_scan<OneCoef>, dim3((g.waves[i] + 3) / 4, cb, 1), dim3(256), 0, st, a, l);
+  if ((g.far >> (l - 2)) & 1u) {
+    hipLaunchKernelGGL(k_coef_fold<OneCoef>, dim3((g.runs[i] + 63) / 64, cb, 1), dim3(1024), 0, st, a, l);
+    hipLaunchKernelGGL(k_coef_prefix<OneCoef>, dim3((g.runs[i] + 63) / 64, cb, 1), dim3(1024), 0, st, a, l);
+  }
   hipLaunchKernelGGL(k_coef_carry<OneCoef>, dim3((g.runs[i] + 3) / 4, cb, 1), dim3(256), 0, st, a, l);
   hipLaunchKernelGGL(k_iter_mul, dim3(std::max(1u, g.carry_mul[i]), cb), dim3(256), 0, st, a, l);
   return hipGetLastError();
@@ -1839,6 +1968,7 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
     if (!by_iteration) q.carried = carried_levels(q, a.sh, cnt);
     std::copy(cnt, cnt + k - 1, counted);
   }
+  q.far = far_levels(q, a.sh, cnt, sized, m, g->info.max_in_degree);
   // bytes a level's scan and products cannot do without: per entry its list
   // entry and the two window rows it reads
   auto level_bytes = [&](uint32_t l) { return (double)counted[l - 2] * (22.0 + 16.0 * width_in(q, l)); };
@@ -2011,6 +2141,7 @@ rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std:
     uint64_t p, q;
     row_bytes(qs[i], cnt + 16 * i, &p, &q);
     qs[i].carried = carried_levels(qs[i], sh[i], cnt + 16 * i);
+    qs[i].far = far_levels(qs[i], sh[i], cnt + 16 * i, true, qs[i].m, graphs[idx[i]]->info.max_in_degree);
     if (p + q > budget) {  // too large for this form: left to the caller
       run[i] = false;
       left->push_back(idx[i]);

@@ -55,3 +55,40 @@ def test_next_window_end_far_past_a_block(arrivals):
                 want = oracle.sieve(g.n, g.src, g.dst, g.t, k, delta, 9, threads=host_threads())
                 assert R.run(gd, k, delta, 9).fingerprint == want
                 assert R.run(gd, k, delta, 9, tuning=R.Tuning(edges_per_tile=16)).fingerprint == want
+
+
+def star_graph(n, m, into, out, tau, seed):
+    """m edges: the share `into` end in vertex 0, the share `out` start there, the rest are random."""
+    r = np.random.default_rng(seed)
+    a, b = int(m * into), int(m * out)
+    src = np.concatenate([r.integers(1, n, a), np.zeros(b), r.integers(1, n, m - a - b)])
+    dst = np.concatenate([np.zeros(a), r.integers(1, n, m - a)])
+    g = inputs.TemporalGraph(n, src.astype(np.uint32), dst.astype(np.uint32), r.integers(1, tau + 1, m).astype(np.uint32),
+                             name=f"star{m}")
+    return inputs.add_colours(g, 4, seed=seed)
+
+
+# One vertex whose arrivals span more runs of a scan than are summed one by one:
+# rows of 3 to 126 coefficients (runs sharing a wave from 262144 entries on, and
+# runs over two blocks of coefficients), single iterations, and, in the batch,
+# long runs.
+@pytest.mark.parametrize("m,k", [(30_000, 3), (150_000, 5), (400_000, 4), (60_000, 9)])
+def test_carries_over_many_runs(m, k):
+    g = star_graph(3000, m, 0.85, 0.08, 2000, seed=k)
+    gd = R.Graph.from_inputs(g)
+    full, queries, want = 1 << k, [], []
+    for delta, motif in ((40, None), (1500, None), (1500, np.array([1, 1, 1, k - 3], np.uint8))):
+        say("[coef] star m", m, "k", k, "delta", delta, "motif", motif is not None)
+        e = R.run(gd, k, delta, 5, motif=motif, per_iteration=True, tuning=R.Tuning(edges_per_tile=16))
+        if k <= 5:
+            kw = dict(colour=g.colour, n_colours=4, motif=motif) if motif is not None else {}
+            assert e.fingerprint == oracle.sieve(g.n, g.src, g.dst, g.t, k, delta, 5, threads=host_threads(), **kw)
+        assert R.run(gd, k, delta, 5, motif=motif).fingerprint == e.fingerprint
+        for lo, hi in ((0, full), (1, 3), (full // 3, full - 1)):
+            r = R.run(gd, k, delta, 5, motif=motif, it_begin=lo, it_end=hi, per_iteration=True)
+            assert np.array_equal(r.per_iteration, e.per_iteration[lo:hi])
+        queries.append(inputs.Query(k=k, delta=delta, seed=5, motif=motif))
+        want.append(e.fingerprint)
+    for q, F in zip(queries, want):
+        assert R.run_batch([gd], [q])[0][0].fingerprint == F
+    assert [r.fingerprint for r in R.run_batch([gd] * 3, queries)[0]] == want
