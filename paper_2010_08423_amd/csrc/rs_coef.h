@@ -64,7 +64,8 @@ struct CoefQuery {
   uint32_t carried;      // bit y: the level with index y has long runs (carries in a launch of their own)
   uint32_t far;          // bit y: a destination of that level may span very many runs (carries from prefix sums)
   uint32_t iters, it0;   // rows by iteration: values per row (0: coefficient rows), iteration of the first
-  const uint64_t* z1;    // rows of single vertices: z, or by iteration z^L [n][iters]
+  uint32_t by_entry;     // by iteration: level 2's rows lie by list entry, not by source
+  const uint64_t* z1;    // rows that level 2 reads: z, or by iteration z^L
   uint32_t z1_stride;
   uint64_t *P, *Q;  // rows of the level below, prefix rows of this level
   uint64_t* tail;        // [runs][C(k, l-1)] XOR of each run's open part

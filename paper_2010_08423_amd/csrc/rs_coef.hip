@@ -768,7 +768,8 @@ __global__ __launch_bounds__(256) void k_coef_lists(A arg) {
     const uint32_t src = Q.e_src[e], dst = Q.e_dst[e], t = Q.e_t[e];
     uint32_t h = kNoRow, o = kNoRow;
     if (l == 2) {
-      h = src;
+      h = Q.by_entry ? p : src;
+      if (Q.by_entry) Q.l_e[p] = src;
     } else {
       const uint2 x = Q.win[e];
       const uint32_t first = Q.in_off[src];
@@ -790,7 +791,7 @@ __global__ __launch_bounds__(256) void k_coef_lists(A arg) {
         comb8(lds_addr(sh.dtab), yv, v);
         yv = gf_reduce(v);
       }
-      Q.l_e[p] = e;
+      if (!Q.iters) Q.l_e[p] = e;
     } else {
       // the block's previous entry, or the rank of the destination's first edge
       const bool starts = i ? Q.e_dst[blockIdx.x * kSetBlock + sh.edge[i - 1]] != dst
@@ -1452,21 +1453,44 @@ __global__ __launch_bounds__(256) void k_coef_pairs(OneCoef a) {
 // Rows by iteration. The value of a single iteration L is no coefficient of the
 // polynomial above, but the product sets, lists and scans serve it as well:
 // with Q.iters set, value i of a row belongs to iteration Q.it0 + i, and a
-// vertex factor is one product by z^L_v = XOR_{j in L} z_{v,j} per value.
+// vertex factor is one product by z^L_v = XOR_{j in L} z_{v,j} per value, formed
+// from the k entries of z_v where it is used.
 // (10^5-edge motif query, k = 9, all 512 iterations: 1400 -> 520 us against the
 // evaluation form, whose lists keep four to eight times the entries. Bound by
 // latency there: 22 launches, each a chain of a few dependent loads.)
 // ---------------------------------------------------------------------------
-// z1[v][i] = z^L_v for L = it0 + i.
-__global__ __launch_bounds__(256) void k_iter_z(OneCoef a, uint64_t* __restrict__ z1) {
+// z^L_v of the lane's iteration (v wave-uniform): the entries of z_v by scalar
+// loads, all in flight together (past the row its last four again, which no bit
+// of L < 2^k selects).
+__device__ __forceinline__ uint64_t iter_form(const CoefQuery& Q, uint32_t v, uint32_t L) {
+  const auto* z = as_const(Q.z + (uint64_t)v * Q.kq);
+  uint64_t x[kCoefMaxK];
+#pragma unroll
+  for (uint32_t j = 0; j < kCoefMaxK; ++j) x[j] = z[min(j & ~3u, Q.kq - 4) + (j & 3u)];
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kCoefMaxK; ++j) {
+    const uint32_t m = 0u - ((L >> j) & 1u);
+    lo = and_xor(lo32(x[j]), m, lo);
+    hi = and_xor(hi32(x[j]), m, hi);
+  }
+  return mk64(lo, hi);
+}
+
+// The rows level 2 reads, at the head of P (whose own rows take over once level
+// 2's scan has read them): z^L of every vertex, or, where there are many vertices
+// for the list (see run_coef), of each entry's source at the entry's place. (3*10^5
+// edges on 3*10^6 vertices, all but one iteration: k = 8, 4044 us by vertex, 217 by
+// entry, 534 in the evaluation form; k = 12, 79.7 ms in a table of 98 GB, 391 us.
+// 2*10^5 edges on 2000 vertices, k = 8: 2277 us by vertex, 2362 by entry.)
+__global__ __launch_bounds__(256) void k_iter_z(OneCoef a) {
   const CoefQuery& Q = a.q;
-  const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (uint64_t)Q.n * Q.iters) return;
-  const uint32_t v = (uint32_t)(idx / Q.iters), L = Q.it0 + (uint32_t)(idx % Q.iters);
-  const uint64_t* z = Q.z + (uint64_t)v * Q.kq;
-  uint64_t x = 0;
-  for (uint32_t j = 0; j < Q.k; ++j) x ^= (L >> j) & 1u ? z[j] : 0;
-  z1[idx] = x;
+  const uint32_t lane = threadIdx.x & 63u, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t n = Q.by_entry ? *as_const(Q.count) : Q.n, co = blockIdx.y * kLanes + lane;
+  for (uint64_t p = blockIdx.x * 4 + wv; p < n; p += gridDim.x * 4) {
+    const uint64_t x = iter_form(Q, Q.by_entry ? as_const(Q.l_e)[p] : (uint32_t)p, Q.it0 + co);
+    if (co < Q.iters) Q.P[p * Q.iters + co] = x;
+  }
 }
 
 // Rows P_l of the entries some window reads: a wave takes 64 values of four
@@ -1500,7 +1524,7 @@ __global__ __launch_bounds__(256) void k_iter_mul(OneCoef a, uint32_t l) {
       const uint32_t dst = as_const(dsts)[p];
       if (dst != cur) {
         cur = dst;
-        gf_table(tab, *(gu64*)(Q.z1 + (uint64_t)dst * C + ca));
+        gf_table(tab, iter_form(Q, dst, Q.it0 + ca));
       }
       Acc128 r = {0, 0, 0, 0};
       gf_comb_acc(base, v, r);
@@ -1535,7 +1559,7 @@ __global__ __launch_bounds__(256) void k_iter_top(OneCoef a) {
   uint64_t sum = 0;
   Acc128 acc = {0, 0, 0, 0};
   auto flush = [&] {
-    if (cur != kNoRow) sum ^= gf_mul(tab, gf_reduce(acc), *(gu64*)(Q.z1 + (uint64_t)cur * C + ca));
+    if (cur != kNoRow) sum ^= gf_mul(tab, gf_reduce(acc), iter_form(Q, cur, Q.it0 + ca));
     acc = Acc128{0, 0, 0, 0};
   };
   for (uint32_t t = t0; t < t1; ++t) {
@@ -1946,11 +1970,7 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
     RS_HIP(launch_coef_sets(a, grid, st));
   }
   uint32_t counted[kCoefMaxK] = {};
-  uint64_t z1_bytes = 0;  // z^L of the vertices, before the P rows
-  auto fits = [&] {
-    z1_bytes = by_iteration ? up(8 * n * q.iters, 256) : 0;
-    return ws.scratch ? z1_bytes + p_bytes + q_bytes <= scratch_left : z1_bytes + p_bytes <= sz.p && q_bytes <= sz.p;
-  };
+  auto fits = [&] { return ws.scratch ? p_bytes + q_bytes <= scratch_left : p_bytes <= sz.p && q_bytes <= sz.p; };
   bool sized = !fits() || p_bytes + q_bytes > kUnsizedRows;
   if (!sized && timed && profiling_on()) {  // the byte accounting wants the sizes
     RS_HIP(hipMemcpyAsync(counted, q.count, 4 * (k - 1), hipMemcpyDeviceToHost, st));
@@ -1969,19 +1989,21 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
     std::copy(cnt, cnt + k - 1, counted);
   }
   q.far = far_levels(q, a.sh, cnt, sized, m, g->info.max_in_degree);
+  // by vertex only where the table fits P, and, the list's size unknown, where it is
+  // small against the edges
+  q.by_entry = by_iteration && n > (sized ? cnt[0] : m / 8) ? 1 : 0;
   // bytes a level's scan and products cannot do without: per entry its list
   // entry and the two window rows it reads
   auto level_bytes = [&](uint32_t l) { return (double)counted[l - 2] * (22.0 + 16.0 * width_in(q, l)); };
   if (ws.scratch) {
-    q.P = reinterpret_cast<uint64_t*>(scratch_rows + z1_bytes);
-    q.Q = reinterpret_cast<uint64_t*>(scratch_rows + z1_bytes + p_bytes);
+    q.P = reinterpret_cast<uint64_t*>(scratch_rows);
+    q.Q = reinterpret_cast<uint64_t*>(scratch_rows + p_bytes);
   } else {
-    p_bytes += z1_bytes;
     // an eighth to spare, so that the next query's slightly larger sets fit too
     if (ws.p0.reserve(p_bytes > ws.p0.bytes ? std::min(sz.p, p_bytes + p_bytes / 8) : 8, st, false) ||
         ws.p1.reserve(q_bytes > ws.p1.bytes ? std::min(sz.p, q_bytes + q_bytes / 8) : 8, st, false))
       return RS_ENOMEM;
-    q.P = reinterpret_cast<uint64_t*>(ws.p0.as<uint8_t>() + z1_bytes);
+    q.P = ws.p0.as<uint64_t>();
     q.Q = ws.p1.as<uint64_t>();
   }
   grid.levels(q, a.sh, cnt);
@@ -1991,14 +2013,13 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
   }
   uint32_t sums_out = grid.top;
   if (by_iteration) {
-    uint64_t* z1 = reinterpret_cast<uint64_t*>(reinterpret_cast<uint8_t*>(q.P) - z1_bytes);
-    q.z1 = z1;
+    q.z1 = q.P;
     q.z1_stride = q.iters;
     const uint32_t top_runs = scan_runs(q, a.sh, cnt[k - 2], k), cb = (q.iters + 63) / 64;
     for (uint32_t i = 0; i < span; i += q.iters) {
       q.it0 = (uint32_t)qp.it_begin + i;
       q.result = sums + i;
-      hipLaunchKernelGGL(k_iter_z, dim3((uint32_t)((n * q.iters + 255) / 256)), dim3(256), 0, st, a, z1);
+      hipLaunchKernelGGL(k_iter_z, dim3(std::max(1u, std::min((uint32_t)((q.by_entry ? cnt[0] : n) + 3) / 4, kMulBlocks)), cb), dim3(256), 0, st, a);
       RS_HIP(hipGetLastError());
       for (uint32_t l = 2; l < k; ++l) {
         ProfScope ps(l == 2 ? KC_FIRST : KC_SCAN, st, level_bytes(l), timed);

@@ -92,3 +92,23 @@ def test_carries_over_many_runs(m, k):
     for q, F in zip(queries, want):
         assert R.run_batch([gd], [q])[0][0].fingerprint == F
     assert [r.fingerprint for r in R.run_batch([gd] * 3, queries)[0]] == want
+
+
+# Single iterations on many vertices: a table of every vertex's z^L would take
+# 8 n 2^k bytes (45 GB) and a launch of more than 2^32 work items.
+@pytest.mark.parametrize("n,k", [(1_400_000, 12), (70_000_000, 6)])
+def test_iterations_on_many_vertices(n, k):
+    m, r = 30_000, np.random.default_rng(k)
+    at = np.sort(r.choice(n, size=600, replace=False))  # the few vertices with edges, over the whole range
+    g = inputs.TemporalGraph(n, at[r.integers(0, 600, m)].astype(np.uint32), at[r.integers(0, 600, m)].astype(np.uint32),
+                             r.integers(1, 400, m).astype(np.uint32), name="spread")
+    gd = R.Graph.from_inputs(g)
+    say("[coef] iterations n", n, "k", k)
+    got = R.run(gd, k, 4, 3, per_iteration=True)
+    small = inputs.TemporalGraph(600, np.searchsorted(at, g.src).astype(np.uint32), np.searchsorted(at, g.dst).astype(np.uint32),
+                                 g.t, name="packed")
+    sd = R.Graph.from_inputs(small)  # the same graph on 600 vertices: other values, the same iterations that vanish
+    assert np.array_equal(got.per_iteration != 0, R.run(sd, k, 4, 3, per_iteration=True).per_iteration != 0)
+    assert got.fingerprint == R.run(gd, k, 4, 3).fingerprint == int(np.bitwise_xor.reduce(got.per_iteration))
+    part = R.run(gd, k, 4, 3, it_begin=8, it_end=24, per_iteration=True, tuning=R.Tuning(edges_per_tile=16))
+    assert np.array_equal(part.per_iteration, got.per_iteration[8:24])
