@@ -2424,14 +2424,14 @@ __device__ __forceinline__ uint64_t lit_terms(const CoefQuery& Q, const LitCoef&
   return gf_reduce(acc);
 }
 
-// Rows of level l (2..k-1), one wave per slot of its set.
+// Rows of level l (2..k-1), one wave per slot of its set (in turn past kLitBlocks
+// blocks).
 __global__ __launch_bounds__(256) void k_litc_level(OneCoef a, LitCoef T, uint32_t l, uint32_t wave_lds, uint64_t* rows) {
   extern __shared__ uint64_t dyn_lds[];  // [4][wave_lds]: tables of a tile, then the row product's
   const CoefQuery& Q = a.q;
   const uint32_t lane = threadIdx.x & 63u, k = Q.k;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t p = blockIdx.x * 4 + wv;
-  if (p >= *as_const(Q.count + (l - 2))) return;
+  const uint32_t n = *as_const(Q.count + (l - 2));
   uint64_t* region = dyn_lds + wv * (wave_lds / 8);
   RowMul M;
   M.c_in = kBinomD.v[k][l - 1];
@@ -2445,13 +2445,16 @@ __global__ __launch_bounds__(256) void k_litc_level(OneCoef a, LitCoef T, uint32
   M.cur = kNoRow;
   M.j0 = 0;
   M.nj = k;
-  const uint4 s = load_const4(T.ls + (uint64_t)(l - 2) * Q.lstride + p);
-  for (uint32_t cb = 0; cb < M.c_in; cb += kLanes) {
-    const uint32_t co = cb + lane;
-    const uint64_t v = lit_terms(Q, T, l, s, M.c_in, min(co, M.c_in - 1), lane, region);
-    if (co < M.c_in) M.q[co] = v;
+  for (uint64_t p = blockIdx.x * 4 + wv; p < n; p += gridDim.x * 4) {
+    const uint4 s = load_const4(T.ls + (uint64_t)(l - 2) * Q.lstride + p);
+    for (uint32_t cb = 0; cb < M.c_in; cb += kLanes) {
+      const uint32_t co = cb + lane;
+      const uint64_t v = lit_terms(Q, T, l, s, M.c_in, min(co, M.c_in - 1), lane, region);
+      if (co < M.c_in) M.q[co] = v;
+    }
+    M.form(a, Q, s.z, rows + p * M.c_out);
+    wave_lds_fence();  // the row has been read before the next one is begun
   }
-  M.form(a, Q, s.z, rows + (uint64_t)p * M.c_out);
 }
 
 // Last level: the value of each slot of its set.
@@ -2489,6 +2492,10 @@ __global__ __launch_bounds__(256) void k_litc_top(OneCoef a, LitCoef T) {
     __hip_atomic_store(Q.result + blockIdx.x, sh.part[0] ^ sh.part[1] ^ sh.part[2] ^ sh.part[3], __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// Blocks of a level's rows at most: a launch takes fewer than 2^32 work items along
+// a dimension, and a level may hold as many slots.
+constexpr uint64_t kLitBlocks = 1 << 20;
 
 bool lit_coef_applies(const LiteralState& L, const QueryPlan& qp) {
   return qp.k >= 3 && coef_applies(qp) && L.ns && L.max_slot_edges <= kLitSlotEdges;
@@ -2562,12 +2569,12 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
     q.P = below;
     const uint32_t lds = mul_lds(k, binom(k, l - 1), binom(k, l)) + kTile * 128;
     if (cnt[l - 2])
-      hipLaunchKernelGGL(k_litc_level, dim3((cnt[l - 2] + 3) / 4), dim3(256), 4 * lds, st, a, T, l, lds, here);
+      hipLaunchKernelGGL(k_litc_level, dim3((uint32_t)std::min<uint64_t>((cnt[l - 2] + 3ull) / 4, kLitBlocks)), dim3(256), 4 * lds, st, a, T, l, lds, here);
     RS_HIP(hipGetLastError());
     std::swap(below, here);
   }
   q.P = below;
-  *n_sums = std::max(1u, std::min((cnt[k - 2] + 3) / 4, kTopBlocks));
+  *n_sums = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((cnt[k - 2] + 3ull) / 4, kTopBlocks));
   hipLaunchKernelGGL(k_litc_top, dim3(*n_sums), dim3(256), 0, st, a, T);
   RS_HIP(hipGetLastError());
   return RS_OK;

@@ -112,3 +112,17 @@ def test_iterations_on_many_vertices(n, k):
     assert got.fingerprint == R.run(gd, k, 4, 3).fingerprint == int(np.bitwise_xor.reduce(got.per_iteration))
     part = R.run(gd, k, 4, 3, it_begin=8, it_end=24, per_iteration=True, tuning=R.Tuning(edges_per_tile=16))
     assert np.array_equal(part.per_iteration, got.per_iteration[8:24])
+
+
+def test_literal_level_of_many_slots():
+    """A level of 67.2*10^6 slots, a wave each: over 2^32 work items in one launch.
+    On a ring whose vertices pass everything on at once, every slot is in the sets."""
+    n, times = 4_200_000, 16
+    v = np.tile(np.arange(n, dtype=np.uint32), times)
+    t = np.repeat(np.arange(1, times + 1, dtype=np.uint32), n)
+    gd = R.Graph(n, v, (v + 1) % np.uint32(n), t)
+    del v, t
+    say("[coef] literal ring")
+    got = R.run_literal(gd, 3, 0, 5)
+    parts = [R.run_literal(gd, 3, 0, 5, it_begin=a, it_end=b).zeta for a, b in ((0, 5), (5, 8))]  # evaluation form
+    assert np.array_equal(got.zeta, parts[0] ^ parts[1]) and (got.reach == 1).all()
