@@ -102,12 +102,16 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
 // The literal reading of one query in the coefficient form: zeta per slot in
 // L.zs; the fingerprint is the XOR of *n_sums words of L.host_result once st is
 // synchronised. *n_sums = 0 (and RS_OK): its rows exceed kLitRows, only scratch
-// was written. A slot's edges are gone over by one thread (sets, lists) or wave
-// (rows), so graphs with more than kLitSlotEdges edges into one vertex at one
-// time are left to the evaluation form, which cuts slots into tiles.
+// was written. A slot's row is formed by one wave, so graphs with more than
+// kLitSlotEdges edges into one vertex at one time are left to the evaluation form,
+// which cuts slots into tiles. So are, up to k = 6, where that form takes a
+// single pass of 64 iterations, graphs whose slots all are long (6*10^4 edges, 25
+// per slot, delta = 5: k = 3, 395 us there and 414 here, k = 6, 653 and 679; k = 9,
+// 3185 and 1241. With 3 per slot and 90 at a hub, k = 3, 1571 and 1439).
 constexpr uint32_t kLitSlotEdges = 128;
+constexpr uint64_t kLitMeanEdges = 8;
 constexpr uint64_t kLitRows = 16ull << 30;  // what the evaluation form's two buffers may hold together
-bool lit_coef_applies(const LiteralState& L, const QueryPlan& qp);
+bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp);
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,
                            hipStream_t st, uint32_t* n_sums);
 

@@ -2238,6 +2238,7 @@ rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std:
 // ---------------------------------------------------------------------------
 struct LitCoef {
   const uint32_t *slot_e, *slot_t, *v_soff;  // edges of a slot [ns + 1], its time, first slot of a vertex
+  const uint32_t* slot;                      // [m] slot of an edge
   uint32_t *wlo, *whi;                       // [m] window of each edge, in slots
   uint64_t* fb;                              // [fwd - 1][words] forward sets of levels 2..fwd
   uint8_t* mark;                             // [k - 2][words * 64] levels 2..k-1: slots some window reads
@@ -2268,6 +2269,7 @@ __global__ __launch_bounds__(1024) void k_litc_begin(OneCoef a, LitCoef T) {
     const uint64_t i0 = (uint64_t)b * 1024 + tid, step = (uint64_t)gridDim.x * 1024, nm = (uint64_t)(Q.k - 2) * Q.words * 8;
     for (uint64_t i = i0; i < nm; i += step) reinterpret_cast<uint64_t*>(T.mark)[i] = 0;
     for (uint64_t i = i0; i < T.ns; i += step) T.zs[i] = 0;
+    for (uint64_t i = Q.words + i0; i < (uint64_t)(Q.fwd - 1) * Q.words; i += step) T.fb[i] = 0;
   }
   if (b < T.nbe) {
     const uint32_t e = b * 1024 + tid;
@@ -2303,79 +2305,116 @@ __global__ __launch_bounds__(1024) void k_litc_begin(OneCoef a, LitCoef T) {
   if (Q.motif && b == T.nbz) shade_det(Q, sh);
 }
 
-// Forward set of level l (3..fwd).
+// The set passes and the lists take an edge per thread, 1024 edges per block: a
+// hub holds any number of edges per slot. (90 per slot, 3*10^5 edges, k = 3, with
+// each slot's edges gone over by the slot's thread: forward pass 42 us, backward
+// passes 82, lists 460, and 12 ms with delta = 400, where an edge's level-2
+// constant sums 401 hashes; 4, 4, 13 and 167 us so.)
+
+// Forward set of level l (3..fwd): the slots of the set below with an edge whose
+// window holds one of its slots. The set's bits are zero before (k_litc_begin).
 __global__ __launch_bounds__(1024) void k_litc_fwd(OneCoef a, LitCoef T, uint32_t l) {
+  __shared__ uint64_t hit[17];  // the slots of 1024 edges
   const CoefQuery& Q = a.q;
   const uint64_t* below = T.fb + (uint64_t)(l - 3) * Q.words;
-  const uint32_t s = blockIdx.x * kSetBlock + threadIdx.x, w = s >> 6;
-  bool in = false;
-  if ((below[w] >> (s & 63u)) & 1u) {  // (bits past ns are zero)
-    const uint32_t e1 = T.slot_e[s + 1];
-    for (uint32_t e = T.slot_e[s]; e < e1 && !in; ++e) {
-      const uint32_t x = T.wlo[e], y = T.whi[e];
-      if (x >= y) continue;
+  uint64_t* here = T.fb + (uint64_t)(l - 2) * Q.words;
+  const uint32_t tid = threadIdx.x, e = blockIdx.x * 1024 + tid, w0 = T.slot[blockIdx.x * 1024] >> 6;
+  if (tid < 17) hit[tid] = 0;
+  __syncthreads();
+  if (e < T.m) {
+    const uint32_t s = T.slot[e], x = T.wlo[e], y = T.whi[e];
+    const uint64_t bit = 1ull << (s & 63u);
+    if (x < y && (below[s >> 6] & bit)) {
+      bool in = false;
       const uint32_t wa = x >> 6, wb = (y - 1) >> 6;
       for (uint32_t i = wa; i <= wb && !in; ++i)
         in = (below[i] & (i == wa ? bits_from(x) : ~0ull) & (i == wb ? bits_below_incl(y - 1) : ~0ull)) != 0;
+      if (in) atomicOr((unsigned long long*)&hit[(s >> 6) - w0], (unsigned long long)bit);
     }
   }
-  const uint64_t f = __ballot(in);
-  if ((threadIdx.x & 63u) == 0) T.fb[(uint64_t)(l - 2) * Q.words + w] = f;
+  __syncthreads();
+  if (tid < 17 && hit[tid]) atomicOr((unsigned long long*)&here[w0 + tid], (unsigned long long)hit[tid]);
 }
 
-// Set of level l (k .. 2) with its ranks; marks its windows for the level below.
+// Is slot s in the set of level l: in the forward set and, below the last
+// level, in a window of the level above.
+__device__ __forceinline__ bool lit_in_set(const CoefQuery& Q, const LitCoef& T, uint32_t l, uint32_t s) {
+  return ((T.fb[(uint64_t)(min(l, Q.fwd) - 2) * Q.words + (s >> 6)] >> (s & 63u)) & 1u) &&
+         (l == Q.k || T.mark[(uint64_t)(l - 2) * Q.words * 64 + s]);
+}
+
+// Set of level l (k .. 2) with its ranks, by the first Q.blocks blocks; the others
+// mark the windows of its edges for the level below.
 __global__ __launch_bounds__(1024) void k_litc_bwd(OneCoef a, LitCoef T, uint32_t l) {
   __shared__ uint64_t sl[16];
   const CoefQuery& Q = a.q;
-  const uint32_t s = blockIdx.x * kSetBlock + threadIdx.x, w = s >> 6;
-  const uint64_t stride = (uint64_t)Q.words * 64;
-  const bool in = ((T.fb[(uint64_t)(min(l, Q.fwd) - 2) * Q.words + w] >> (s & 63u)) & 1u) &&
-                  (l == Q.k || T.mark[(l - 2) * stride + s]);
-  if (in && l > 2) {
-    uint8_t* mk = T.mark + (l - 3) * stride;
-    const uint32_t e1 = T.slot_e[s + 1];
-    for (uint32_t e = T.slot_e[s]; e < e1; ++e) {
-      const uint32_t y = T.whi[e];
-      for (uint32_t q = T.wlo[e]; q < y; ++q) mk[q] = 1;
-    }
+  if (blockIdx.x >= Q.blocks) {
+    const uint32_t e = (blockIdx.x - Q.blocks) * 1024 + threadIdx.x;
+    if (l == 2 || e >= T.m || !lit_in_set(Q, T, l, T.slot[e])) return;
+    uint8_t* mk = T.mark + (uint64_t)(l - 3) * Q.words * 64;
+    const uint32_t y = T.whi[e];
+    for (uint32_t q = T.wlo[e]; q < y; ++q) mk[q] = 1;
+    return;
   }
-  set_word(Q, l - 2, w, __ballot(in), sl);
+  const uint32_t s = blockIdx.x * kSetBlock + threadIdx.x;
+  set_word(Q, l - 2, s >> 6, __ballot(lit_in_set(Q, T, l, s)), sl);
   set_ranks(Q, l - 2, blockIdx.x, sl);
 }
 
-// Lists of levels 2..k, one block per 1024 slots and level (as k_coef_lists).
+// Lists of levels 2..k (as k_coef_lists): the first Q.blocks blocks of a level
+// write its slots, the others its edges, 1024 each. Either gathers what is in the
+// set in LDS first, so that all lanes are busy.
 __global__ __launch_bounds__(256) void k_litc_lists(OneCoef a, LitCoef T) {
   __shared__ uint16_t at[kSetBlock];
+  __shared__ uint32_t count;
   const CoefQuery& Q = a.q;
-  const uint32_t y = blockIdx.y, l = y + 2, lane = threadIdx.x & 63u;
-  const uint32_t n = Q.bsum[(uint64_t)y * Q.blocks + blockIdx.x];
-  if (n == 0) return;
+  const uint32_t y = blockIdx.y, l = y + 2, lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint64_t* bits = Q.sbits + (uint64_t)y * Q.words;
+  if (blockIdx.x < Q.blocks) {
+    const uint32_t n = Q.bsum[(uint64_t)y * Q.blocks + blockIdx.x];
+    if (n == 0) return;
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+      const uint32_t lw = r * 4 + wv, w = blockIdx.x * 16 + lw;
+      const uint64_t b = bits[w];
+      if ((b >> lane) & 1ull)
+        at[Q.wrank[(uint64_t)y * Q.words + w] + __popcll(b & ((1ull << lane) - 1))] = (uint16_t)(lw * 64 + lane);
+    }
+    __syncthreads();
+    const uint64_t p0 = y * Q.lstride + Q.boff[(uint64_t)y * Q.blocks + blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+      const uint32_t s = blockIdx.x * kSetBlock + at[i], e0 = T.slot_e[s];
+      T.ls[p0 + i] = make_uint4(e0, T.slot_e[s + 1], Q.e_dst[e0], s);
+      T.rt[p0 + i] = T.slot_t[s];
+    }
+    return;
+  }
+  const uint32_t eb = (blockIdx.x - Q.blocks) * 1024;
+  if (threadIdx.x == 0) count = 0;
+  __syncthreads();
 #pragma unroll
   for (uint32_t r = 0; r < 4; ++r) {
-    const uint32_t lw = r * 4 + (threadIdx.x >> 6);
-    const uint64_t i = (uint64_t)y * Q.words + blockIdx.x * 16 + lw;
-    const uint64_t bits = Q.sbits[i];
-    if ((bits >> lane) & 1ull) at[Q.wrank[i] + __popcll(bits & ((1ull << lane) - 1))] = (uint16_t)(lw * 64 + lane);
+    const uint32_t i = r * 256 + threadIdx.x, s = eb + i < T.m ? T.slot[eb + i] : 0u;
+    const uint64_t in = __ballot(eb + i < T.m && ((bits[s >> 6] >> (s & 63u)) & 1u));
+    uint32_t p = 0;
+    if (lane == 0 && in) p = atomicAdd(&count, (uint32_t)__popcll(in));
+    p = __shfl(p, 0, 64);
+    if ((in >> lane) & 1u) at[p + __popcll(in & ((1ull << lane) - 1))] = (uint16_t)i;
   }
   __syncthreads();
-  const uint64_t p0 = y * Q.lstride + Q.boff[(uint64_t)y * Q.blocks + blockIdx.x];
   uint4* te = T.te + (uint64_t)y * T.m;
+  const uint32_t n = count;
   for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const uint32_t s = blockIdx.x * kSetBlock + at[i], e0 = T.slot_e[s], e1 = T.slot_e[s + 1], u = Q.e_dst[e0];
-    T.ls[p0 + i] = make_uint4(e0, e1, u, s);
-    T.rt[p0 + i] = T.slot_t[s];
-    for (uint32_t e = e0; e < e1; ++e) {
-      const uint32_t v = Q.e_src[e];
-      const uint64_t h = lit_edge_key(T.hp, v, u);
-      if (l == 2) {
-        const uint32_t t = Q.e_t[e], dv = Q.dv ? Q.dv[v] : Q.delta;
-        uint64_t y2 = 0;  // the window sum of y over every time t - j >= 1, j <= delta(v)
-        for (uint64_t p = t > dv ? t - dv : 1u; p <= t; ++p) y2 ^= lit_y(h, (uint32_t)p, 1);
-        te[e] = make_uint4(v, 1, lo32(y2), hi32(y2));
-      } else {
-        const uint32_t ra = set_rank(Q, y - 1, T.wlo[e]), rb = set_rank(Q, y - 1, T.whi[e]);
-        te[e] = make_uint4(ra, rb - ra, lo32(h), hi32(h));
-      }
+    const uint32_t e = eb + at[i], v = Q.e_src[e];
+    const uint64_t h = lit_edge_key(T.hp, v, Q.e_dst[e]);
+    if (l == 2) {
+      const uint32_t t = Q.e_t[e], dv = Q.dv ? Q.dv[v] : Q.delta;
+      uint64_t y2 = 0;  // the window sum of y over every time t - j >= 1, j <= delta(v)
+      for (uint64_t p = t > dv ? t - dv : 1u; p <= t; ++p) y2 ^= lit_y(h, (uint32_t)p, 1);
+      te[e] = make_uint4(v, 1, lo32(y2), hi32(y2));
+    } else {
+      const uint32_t ra = set_rank(Q, y - 1, T.wlo[e]), rb = set_rank(Q, y - 1, T.whi[e]);
+      te[e] = make_uint4(ra, rb - ra, lo32(h), hi32(h));
     }
   }
 }
@@ -2497,8 +2536,9 @@ __global__ __launch_bounds__(256) void k_litc_top(OneCoef a, LitCoef T) {
 // a dimension, and a level may hold as many slots.
 constexpr uint64_t kLitBlocks = 1 << 20;
 
-bool lit_coef_applies(const LiteralState& L, const QueryPlan& qp) {
-  return qp.k >= 3 && coef_applies(qp) && L.ns && L.max_slot_edges <= kLitSlotEdges;
+bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp) {
+  return qp.k >= 3 && coef_applies(qp) && L.ns && L.max_slot_edges <= kLitSlotEdges &&
+         (qp.k > 6 || m <= kLitMeanEdges * L.ns);
 }
 
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,
@@ -2517,6 +2557,7 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
   T.slot_e = L.slot_e.as<uint32_t>();
   T.slot_t = L.slot_t.as<uint32_t>();
   T.v_soff = L.v_soff.as<uint32_t>();
+  T.slot = L.slot.as<uint32_t>();
   T.m = (uint32_t)m;
   T.ns = (uint32_t)ns;
   T.hp = hp;
@@ -2549,8 +2590,9 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
   {
     ProfScope ps(KC_LITERAL, st, 0.0);
     hipLaunchKernelGGL(k_litc_begin, dim3(T.nbe + q.blocks + T.nbz + q.motif), dim3(1024), 0, st, a, T);
-    for (uint32_t l = 3; l <= q.fwd; ++l) hipLaunchKernelGGL(k_litc_fwd, dim3(q.blocks), dim3(1024), 0, st, a, T, l);
-    for (uint32_t l = k; l >= 2; --l) hipLaunchKernelGGL(k_litc_bwd, dim3(q.blocks), dim3(1024), 0, st, a, T, l);
+    for (uint32_t l = 3; l <= q.fwd; ++l) hipLaunchKernelGGL(k_litc_fwd, dim3(T.nbe), dim3(1024), 0, st, a, T, l);
+    for (uint32_t l = k; l >= 2; --l)
+      hipLaunchKernelGGL(k_litc_bwd, dim3(q.blocks + (l > 2 ? T.nbe : 0)), dim3(1024), 0, st, a, T, l);
     hipLaunchKernelGGL(k_coef_offsets<OneCoef>, dim3(k - 1, 1), dim3(1024), 0, st, a);
     RS_HIP(hipGetLastError());
   }
@@ -2562,7 +2604,7 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
   if (2 * rows > kLitRows) return RS_OK;
   if (L.chi0.reserve(rows, st, false) || L.chi1.reserve(rows, st, false)) return RS_ENOMEM;
   ProfScope ps(KC_LITERAL, st, 0.0);
-  hipLaunchKernelGGL(k_litc_lists, dim3(q.blocks, k - 1), dim3(256), 0, st, a, T);
+  hipLaunchKernelGGL(k_litc_lists, dim3(q.blocks + T.nbe, k - 1), dim3(256), 0, st, a, T);
   RS_HIP(hipGetLastError());
   uint64_t *below = L.chi0.as<uint64_t>(), *here = L.chi1.as<uint64_t>();
   for (uint32_t l = 2; l < k; ++l) {

@@ -28,7 +28,7 @@
 // window reads.
 //
 // This form runs parts of the iteration range, k outside 3..12 and graphs with
-// very long slots; other queries take the coefficient form (rs_coef.hip), whose
+// long slots (see rs_coef.h); other queries take the coefficient form (rs_coef.hip), whose
 // rows hold C(k,l) values per slot instead of 2^k and whose slots are only
 // those on a walk of k vertices (10^6-edge path query, k = 8: 5.2 -> 1.2 ms).
 #include <rocprim/device/device_scan.hpp>
@@ -552,7 +552,7 @@ static rs_status run_literal(rs_graph* g, const QueryPlan& qp, const uint32_t* d
   const uint64_t hp = mix64_host(qp.seed + (uint64_t)'P' * 0x9E3779B97F4A7C15ull);
   // The coefficient form where it applies (rs_coef.hip: whole ranges, 3 <= k <= 12)
   uint32_t n_sums = 0;
-  if (lit_coef_applies(L, qp)) RS_TRY(run_literal_coef(G, L, qp, dv, hp, st, &n_sums));
+  if (lit_coef_applies(L, m, qp)) RS_TRY(run_literal_coef(G, L, qp, dv, hp, st, &n_sums));
   if (!n_sums) RS_TRY(run_literal_eval(G, L, qp, dv, hp, st));
   RS_HIP(launch_fill32(L.reach.as<uint32_t>(), 0xFFFFFFFFu, n, st));
   uint64_t F = 0;

@@ -126,3 +126,23 @@ def test_literal_level_of_many_slots():
     got = R.run_literal(gd, 3, 0, 5)
     parts = [R.run_literal(gd, 3, 0, 5, it_begin=a, it_end=b).zeta for a, b in ((0, 5), (5, 8))]  # evaluation form
     assert np.array_equal(got.zeta, parts[0] ^ parts[1]) and (got.reach == 1).all()
+
+
+# Slots of very uneven length: a hub's with up to 128 edges next to single ones,
+# blocks of 1024 edges that hold a few slots, a part of one, or a thousand.
+@pytest.mark.parametrize("k,delta", [(3, 4), (5, 60), (7, 4), (8, 20)])
+def test_literal_uneven_slots(k, delta):
+    r = np.random.default_rng(k)
+    n, hubs = 1200, 9000
+    src = np.concatenate([r.integers(0, n, 3 * hubs), r.integers(0, n, 4000), np.zeros(600), np.full(500, n - 1)])
+    dst = np.concatenate([np.zeros(hubs), np.full(hubs, 600), np.full(hubs, n - 1), r.integers(0, n, 5100)])
+    t = np.concatenate([1 + np.arange(3 * hubs) % hubs // 100, r.integers(1, 300, 5100)])
+    g = inputs.TemporalGraph(n, *(x.astype(np.uint32) for x in (src, dst, t)), name="uneven")
+    inputs.add_colours(g, 4, seed=k)
+    gd = R.Graph.from_inputs(g)
+    for motif in (None, np.array([1, 1, 0, k - 2], np.uint8)):
+        kw = dict(colour=g.colour, n_colours=4, motif=motif) if motif is not None else {}
+        say("[coef] literal uneven slots k", k, "delta", delta)
+        z, reach = oracle.fine_literal(g.n, g.src, g.dst, g.t, k, delta, 17, threads=host_threads(), **kw)
+        got = R.run_literal(gd, k, delta, 17, motif=motif)
+        assert np.array_equal(got.zeta, z) and np.array_equal(got.reach, reach)
