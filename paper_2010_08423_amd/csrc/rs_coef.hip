@@ -1322,8 +1322,8 @@ __global__ __launch_bounds__(256) void k_coef_top(A arg, uint32_t per_wave) {
   const uint32_t inv = 65536 / k + 1;  // i / k = i * inv >> 16 for i < 64 k
   uint64_t sum = 0;
   const uint32_t rounds = (per_wave * k + kLanes - 1) / kLanes;
-  for (uint32_t p0 = (blockIdx.x * 4 + wv) * per_wave; p0 < n; p0 += gridDim.x * 4 * per_wave) {
-    const uint32_t p = p0 + lane;
+  for (uint64_t p0 = (blockIdx.x * 4 + wv) * per_wave; p0 < n; p0 += gridDim.x * 4 * per_wave) {
+    const uint32_t p = (uint32_t)p0 + lane;
     const bool in = lane < per_wave && p < n;
     const uint32_t h = in ? Q.l_hi[lo + p] : kNoRow, o = in ? Q.l_lo[lo + p] : kNoRow, dst = in ? Q.l_dst[lo + p] : 0u;
     const uint64_t yv = in ? Q.l_y[lo + p] : 0;
@@ -1410,7 +1410,7 @@ __global__ __launch_bounds__(256) void k_coef_pairs(OneCoef a) {
   auto omega = [&](uint32_t d, uint32_t j) { return hash1(Q.seed, 'W', (uint64_t)d | ((uint64_t)(j + 1) << 32)); };
   const uint64_t det = Q.motif ? gf_mul(tab, omega(0, 0), omega(1, 1)) ^ gf_mul(tab, omega(0, 1), omega(1, 0)) : 0;
   uint64_t sum = 0;
-  for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < Q.m; e += gridDim.x * 256) {
+  for (uint64_t e = blockIdx.x * 256 + threadIdx.x; e < Q.m; e += gridDim.x * 256) {  // (m may be near 2^32)
     const uint32_t s = Q.e_src[e], u = Q.e_dst[e], t = Q.e_t[e];
     bool ok = !(Q.f.rmask && (Q.f.rmask[s] | Q.f.rmask[u])) && !(Q.f.t_max && t > Q.f.t_max) &&
               !(Q.f.smask && !Q.f.smask[s]) && !(Q.f.tmask && !Q.f.tmask[u]);
@@ -2510,7 +2510,7 @@ __global__ __launch_bounds__(256) void k_litc_top(OneCoef a, LitCoef T) {
   tab[0] = 0;
   const uint32_t n = *as_const(Q.count + (k - 2)), ca = min(lane, k - 1);
   uint64_t sum = 0;
-  for (uint32_t p = blockIdx.x * 4 + wv; p < n; p += gridDim.x * 4) {
+  for (uint64_t p = blockIdx.x * 4 + wv; p < n; p += gridDim.x * 4) {
     const uint4 s = load_const4(T.ls + (uint64_t)(k - 2) * Q.lstride + p);
     const uint64_t z = lane < k ? *(gu64*)(Q.z + (uint64_t)s.z * Q.kq + (k - 1 - lane)) : 0;
     uint64_t v = gf_mul(tab, lit_terms(Q, T, k, s, k, ca, lane, sh.ytab[wv]), z);

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(1024) void k_pick_least(const uint32_t* __restrict_
   if (threadIdx.x == 0) least = ~0ull;
   __syncthreads();
   unsigned long long x = ~0ull;
-  for (uint32_t u = blockIdx.x * 1024 + threadIdx.x; u < n; u += gridDim.x * 1024)
+  for (uint64_t u = blockIdx.x * 1024 + threadIdx.x; u < n; u += gridDim.x * 1024)
     if (reach[u] != 0xFFFFFFFFu) x = min(x, (unsigned long long)reach[u] << 32 | u);
   if (x != ~0ull) atomicMin(&least, x);
   __syncthreads();

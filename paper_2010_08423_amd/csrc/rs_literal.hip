@@ -170,7 +170,7 @@ __global__ __launch_bounds__(1024) void k_lit_longest(const uint32_t* __restrict
   if (threadIdx.x == 0) most = 0;
   __syncthreads();
   uint32_t c = 0;
-  for (uint32_t s = blockIdx.x * 1024 + threadIdx.x; s < ns; s += gridDim.x * 1024) c = max(c, slot_e[s + 1] - slot_e[s]);
+  for (uint64_t s = blockIdx.x * 1024 + threadIdx.x; s < ns; s += gridDim.x * 1024) c = max(c, slot_e[s + 1] - slot_e[s]);
   atomicMax(&most, c);
   __syncthreads();
   if (threadIdx.x == 0) atomicMax(out, most);
