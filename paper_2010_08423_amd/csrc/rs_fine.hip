@@ -74,21 +74,48 @@ __global__ __launch_bounds__(256) void k_top_fine(const uint32_t* __restrict__ e
 
 // Per slot (u, i) (a maximal run of edges with equal dst and t, starting at an
 // edge e in [e0, e1) whose predecessor differs): zeta = XOR of T over the run, written
-// to every edge of the run; a non-zero zeta lowers reach[u] to i.
+// to every edge of the run; a non-zero zeta lowers reach[u] to i. A thread goes
+// over up to kSlotAlone edges of its slot, the wave over the rest of the longer
+// ones, 64 at a time. (10^6 edges in eight launches, slots of 700 edges at a hub:
+// 171 us per launch with the slot's thread alone, 30 so.)
+constexpr uint32_t kSlotAlone = 16;
 __global__ __launch_bounds__(256) void k_fine_slots(const uint32_t* __restrict__ e_dst, const uint32_t* __restrict__ e_t,
                                                     const uint64_t* __restrict__ T, uint32_t m, uint32_t e0, uint32_t e1,
                                                     uint64_t* __restrict__ zeta, uint32_t* __restrict__ reach) {
   const uint64_t e = e0 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= e1) return;
-  const uint32_t u = e_dst[e], t = e_t[e];
-  if (e > 0 && e_dst[e - 1] == u && e_t[e - 1] == t) return;  // not the first edge of its slot
-  uint64_t acc = 0;
-  uint64_t f = e;
-  for (; f < m && e_dst[f] == u && e_t[f] == t; ++f) acc ^= T[f];
-  for (uint64_t g = e; g < f; ++g) zeta[g] = acc;
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t u = 0, t = 0;
+  uint64_t acc = 0, f = e;  // the slot's edges [e, f) are summed
+  bool mine = e < e1, more = false;
+  if (mine) {
+    u = e_dst[e];
+    t = e_t[e];
+    mine = e == 0 || e_dst[e - 1] != u || e_t[e - 1] != t;  // else not the first edge of its slot
+  }
+  if (mine) {
+    for (; f < m && f < e + kSlotAlone && e_dst[f] == u && e_t[f] == t; ++f) acc ^= T[f];
+    more = f == e + kSlotAlone && f < m && e_dst[f] == u && e_t[f] == t;
+    if (!more)
+      for (uint64_t g = e; g < f; ++g) zeta[g] = acc;
+  }
+  for (uint64_t rest = __ballot(more); rest; rest &= rest - 1) {
+    const int o = __builtin_ctzll(rest);
+    const uint32_t su = __shfl(u, o), st = __shfl(t, o), first = (uint32_t)__shfl((uint32_t)e, o);
+    uint64_t x = (uint64_t)first + kSlotAlone, v = lane == (uint32_t)o ? acc : 0, in;
+    do {
+      const uint64_t g = x + lane;
+      const bool same = g < m && e_dst[g] == su && e_t[g] == st;
+      if (same) v ^= T[g];
+      in = __ballot(same);  // (the slot's edges are consecutive)
+      x += __builtin_popcountll(in);
+    } while (in == ~0ull);
+    v = wave_xor(v);
+    if (lane == (uint32_t)o) acc = v;
+    for (uint64_t g = first + lane; g < x; g += 64) zeta[g] = v;
+  }
   // (the plain load spares the slots after a vertex's first an atomic on its word; an
   // old value read costs one)
-  if (acc && t < reach[u]) atomicMin(&reach[u], t);
+  if (mine && acc && t < reach[u]) atomicMin(&reach[u], t);
 }
 
 // Product rows [m][kq] of the one level of a k = 2 query with the query's

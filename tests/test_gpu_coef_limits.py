@@ -146,3 +146,28 @@ def test_literal_uneven_slots(k, delta):
         z, reach = oracle.fine_literal(g.n, g.src, g.dst, g.t, k, delta, 17, threads=host_threads(), **kw)
         got = R.run_literal(gd, k, delta, 17, motif=motif)
         assert np.array_equal(got.zeta, z) and np.array_equal(got.reach, reach)
+
+
+# Per-slot outputs around the slot length from which a wave goes on where the
+# slot's thread stops (16 edges, then 64 at a time), and, from 262144 edges on,
+# written in eight parts of the edges with slots across their ends.
+@pytest.mark.parametrize("lengths", [(1, 15, 16, 17, 18, 79, 80, 81, 144, 145, 300), (900,) * 310, (70_000,) * 4])
+def test_slots_of_every_length(lengths):
+    r = np.random.default_rng(len(lengths))
+    n = max(lengths) + 2
+    src = [np.sort(r.choice(n - 1, size=x, replace=False)) for x in lengths]
+    into = np.repeat(np.arange(len(lengths)) % 7, lengths)  # seven vertices, a slot per time
+    t = np.repeat(10 + np.arange(len(lengths)) // 7, lengths)
+    src = np.concatenate([*src, r.integers(0, n, 500)])
+    dst = np.concatenate([np.where(src[:len(into)] == into, n - 1, into), r.integers(0, n, 500)])
+    g = inputs.TemporalGraph(n, src.astype(np.uint32), dst.astype(np.uint32),
+                             np.concatenate([t, r.integers(1, 12, 500)]).astype(np.uint32), name="lengths")
+    gd = R.Graph.from_inputs(g)
+    for k in (2, 3, 4):
+        say("[coef] slots of up to", max(lengths), "edges, m", len(g.src), "k", k)
+        z, reach, F = oracle.fine_grained(g.n, g.src, g.dst, g.t, k, 6, 5, threads=host_threads())
+        for it_end in (0, 1 << k):  # (the second run reuses the output buffer)
+            got = R.run_fine(gd, k, 6, 5, it_end=it_end)
+            assert got.fingerprint == F and np.array_equal(got.reach, reach) and np.array_equal(got.zeta, z)
+        only = R.run_fine(gd, k, 6, 5, slots=False)
+        assert only.zeta is None and np.array_equal(only.reach, reach)
