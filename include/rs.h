@@ -249,7 +249,10 @@ rs_status rs_run_constrained(const rs_graph* g, const rs_query* q, const rs_cons
  * of the canonical list (rs_graph_edges order), the zeta of its slot
  * (dst, t). r->fingerprint is the XOR of all zeta (the rs_run_constrained
  * fingerprint), r->yes says D is not empty. The iteration range of q selects
- * the iterations summed. */
+ * the iterations summed. From 262144 edges on, slot_zeta is written through
+ * pinned host memory of 8 info.m + 4 n bytes, which the graph keeps (one buffer
+ * for this call and rs_run_literal) until it is destroyed; outputs above 256 MiB
+ * do without. */
 rs_status rs_run_fine(const rs_graph* g, const rs_query* q, const rs_constraints* c, uint32_t* reach_time,
                       uint64_t* slot_zeta, rs_result* r, void* hip_stream);
 

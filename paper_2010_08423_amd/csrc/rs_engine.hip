@@ -12,7 +12,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -449,7 +448,7 @@ rs_status FineOut::run(uint64_t* zeta, uint64_t* zeta_dev, uint64_t m, uint32_t*
                        uint64_t n, hipStream_t st, hipEvent_t done,
                        const std::function<hipError_t(uint32_t, uint32_t, uint64_t*)>& launch) {
   const size_t z_bytes = (8 * m + 255) / 256 * 256;
-  if (!zeta || m < kLeast || !reserve(z_bytes + 4 * n)) {
+  if (!zeta || m < kLeast || z_bytes + 4 * n > kMost || !reserve(z_bytes + 4 * n)) {
     RS_HIP(launch(0, (uint32_t)m, zeta_dev));
     if (done) RS_HIP(hipEventRecord(done, st));
     if (n) RS_HIP(hipMemcpyAsync(reach, reach_dev, 4 * n, hipMemcpyDeviceToHost, st));
@@ -487,7 +486,7 @@ rs_status FineOut::run(uint64_t* zeta, uint64_t* zeta_dev, uint64_t m, uint32_t*
   for (uint32_t t = 1; t < kThreads; ++t) {
     try {
       th[t] = std::thread(work, t);
-    } catch (const std::system_error&) {  // the others take its parts
+    } catch (...) {  // (none to be had: the others take its parts)
       break;
     }
   }
@@ -500,8 +499,9 @@ rs_status FineOut::run(uint64_t* zeta, uint64_t* zeta_dev, uint64_t m, uint32_t*
 }
 
 // Outputs of a fine-grained query from its per-edge sums; returns once st's work is done.
-static rs_status fine_outputs(const GraphDev& G, PlainWorkspace& ws, const QueryPlan& qp, const uint32_t* dv,
+static rs_status fine_outputs(rs_graph* g, PlainWorkspace& ws, const QueryPlan& qp, const uint32_t* dv,
                               QueryExtras* ex, hipStream_t st) {
+  const GraphDev& G = g->g;
   uint32_t* reach = ws.fine_r.as<uint32_t>();
   if (ex->pick) {
     if (!ws.pick_host) RS_HIP(hipHostMalloc((void**)&ws.pick_host, 8 * kPickWords, hipHostMallocDefault));
@@ -513,7 +513,7 @@ static rs_status fine_outputs(const GraphDev& G, PlainWorkspace& ws, const Query
     ex->reached = ex->pick->vertex != 0xFFFFFFFFu;
     return RS_OK;
   }
-  return ws.fine_out.run(ex->zeta, ws.fine_z.as<uint64_t>(), G.m, ex->reach, reach, G.n, st, nullptr,
+  return g->fine_out.run(ex->zeta, ws.fine_z.as<uint64_t>(), G.m, ex->reach, reach, G.n, st, nullptr,
                          [&](uint32_t e0, uint32_t e1, uint64_t* zeta) {
                            return launch_fine_slots(G.e_dst.as<uint32_t>(), G.e_t.as<uint32_t>(),
                                                     ws.fine_t.as<uint64_t>(), (uint32_t)G.m, e0, e1, zeta, reach, st);
@@ -589,7 +589,7 @@ rs_status run_plain(rs_graph* g, PlainWorkspace& ws, const QueryPlan& qp, const 
     if (n_sums) {
       if (fine) {
         RS_HIP(launch_fill32(ws.fine_r.as<uint32_t>(), 0xFFFFFFFFu, n, st));
-        RS_TRY(fine_outputs(G, ws, qp, dv, ex, st));
+        RS_TRY(fine_outputs(g, ws, qp, dv, ex, st));
       }
       if (timed) RS_HIP(hipEventRecord(ws.ev1, st));
       RS_HIP(hipStreamSynchronize(st));
@@ -881,7 +881,7 @@ rs_status run_plain(rs_graph* g, PlainWorkspace& ws, const QueryPlan& qp, const 
       // zeta per slot, reach times; F = the XOR of the per-edge sums
       RS_HIP(launch_xor_reduce(ws.fine_t.as<uint64_t>(), 0, m, ws.out.as<uint64_t>(), st));
       RS_HIP(hipMemcpyAsync(&F, ws.out.p, 8, hipMemcpyDeviceToHost, st));
-      RS_TRY(fine_outputs(G, ws, qp, dv, ex, st));
+      RS_TRY(fine_outputs(g, ws, qp, dv, ex, st));
       if (timed) RS_HIP(hipEventRecord(ws.ev1, st));
       RS_HIP(hipStreamSynchronize(st));
       if (count_lb) {
@@ -1049,6 +1049,7 @@ rs_status rs_graph_destroy(rs_graph* g) {
     b->release();
   g->ws.release();
   g->lit.release();
+  g->fine_out.release();
   delete g;
   return RS_OK;
 }

@@ -357,14 +357,16 @@ uint64_t table_need_bytes(uint64_t m, uint32_t k);
 // the edges, and up to four threads copy a part on while the next one is
 // written. (10^6 edges, 8.4 MB, wait included: 660 us by the runtime's pageable
 // copy, which moves 1 MB and then copies it; 480 us through a pinned ring of
-// 512 KB pieces, one copy launch each; about 330 so.)
+// 512 KB pieces, one copy launch each; about 330 so.) The pinned buffer holds the
+// whole output, so outputs past kMost bytes go by the pageable copy.
 struct FineOut {
   static constexpr uint32_t kParts = 8, kThreads = 4;
   static constexpr uint64_t kLeast = 256 << 10;  // edges; fewer go by the pageable copy (2 MB: 130 us either way)
+  static constexpr uint64_t kMost = 256 << 20;   // bytes
   uint8_t* buf = nullptr;
   size_t bytes = 0;
   hipEvent_t ev[kParts + 1] = {};
-  // launch(e0, e1, zeta, last): writes the values of the slots that start in
+  // launch(e0, e1, zeta): writes the values of the slots that start in
   // edges [e0, e1). Returns once st's work is done and the caller's arrays are
   // filled; zeta_dev is used where the values don't go through pinned memory.
   // done, unless null, is recorded behind the device's work.
@@ -478,7 +480,6 @@ struct PlainWorkspace {
   uint32_t epoch = 0;
   uint64_t p_elems_per_chunk = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  FineOut fine_out;
   uint64_t* pick_host = nullptr;    // pinned: a picked slot
   uint64_t* host_result = nullptr;  // pinned: where the coefficient form's last kernel leaves the fingerprint
   uint8_t* scratch = nullptr;  // borrowed region (no-allocation workspace), or null
@@ -501,7 +502,6 @@ struct PlainWorkspace {
     if (ev1) (void)hipEventDestroy(ev1);
     if (pick_host) (void)hipHostFree(pick_host);
     pick_host = nullptr;
-    fine_out.release();
     ev0 = ev1 = nullptr;
     if (host_result) (void)hipHostFree(host_result);
     host_result = nullptr;
@@ -544,7 +544,6 @@ struct LiteralState {
   DevBuf slot, slot_t, slot_e, v_soff;
   DevBuf coef;                      // sets and lists of the coefficient form
   uint64_t* host_result = nullptr;  // its sums (pinned)
-  FineOut fine_out;
   DevBuf wlo, whi, y2, need, z, zs, out, chi0, chi1, dv, reach, zeta_edge;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   void release() {
@@ -556,7 +555,6 @@ struct LiteralState {
     ev0 = ev1 = nullptr;
     if (host_result) (void)hipHostFree(host_result);
     host_result = nullptr;
-    fine_out.release();
     built = false;
   }
 };
@@ -581,4 +579,5 @@ struct rs_graph {
   std::map<std::pair<uint32_t, uint32_t>, std::vector<rs::NeedCounts>> need_counts;  // by (delta, k), per level
   rs::DevBuf counts_dev;
   rs::LiteralState lit;  // literal-reading sieve (rs_run_literal); guarded by mu
+  rs::FineOut fine_out;  // per-slot outputs of rs_run_fine and rs_run_literal; guarded by mu
 };

@@ -558,7 +558,7 @@ static rs_status run_literal(rs_graph* g, const QueryPlan& qp, const uint32_t* d
   uint64_t F = 0;
   if (!n_sums) RS_HIP(hipMemcpyAsync(&F, L.out.p, 8, hipMemcpyDeviceToHost, st));
   uint32_t* reach = L.reach.as<uint32_t>();
-  RS_TRY(L.fine_out.run(slot_zeta, slot_zeta ? L.zeta_edge.as<uint64_t>() : nullptr, m, reach_time, reach, n, st, L.ev1,
+  RS_TRY(g->fine_out.run(slot_zeta, slot_zeta ? L.zeta_edge.as<uint64_t>() : nullptr, m, reach_time, reach, n, st, L.ev1,
                         [&](uint32_t e0, uint32_t e1, uint64_t* zeta) {
                           return lit_outputs(G, L, e0, e1, zeta, reach, st);
                         }));

@@ -171,3 +171,13 @@ def test_slots_of_every_length(lengths):
             assert got.fingerprint == F and np.array_equal(got.reach, reach) and np.array_equal(got.zeta, z)
         only = R.run_fine(gd, k, 6, 5, slots=False)
         assert only.zeta is None and np.array_equal(only.reach, reach)
+
+
+def test_outputs_of_both_readings_share_a_buffer():
+    g = inputs.chung_lu_graph(30_000, 300_000, 2.4, 800, seed=9)
+    gd = R.Graph.from_inputs(g)
+    fine = oracle.fine_grained(g.n, g.src, g.dst, g.t, 4, 6, 5, threads=host_threads())
+    lit = oracle.fine_literal(g.n, g.src, g.dst, g.t, 4, 6, 5, threads=host_threads())
+    for _ in range(2):
+        for want, got in ((fine, R.run_fine(gd, 4, 6, 5)), (lit, R.run_literal(gd, 4, 6, 5))):
+            assert np.array_equal(got.zeta, want[0]) and np.array_equal(got.reach, want[1])
