@@ -378,7 +378,7 @@ struct BatchWorkspace {
   std::mutex mu;
   DevBuf qs, units, ubegin, per_query, parena, agg, incl, out, ref, cov, bounds;
   DevBuf lb;  // look-back counters [2] (while counting is on)
-  CoefBatch* coef = coef_batch_create();  // queries run in the coefficient form
+  CoefBatch* coef = coef_batch_create();  // queries run in the coefficient form, in per_query and parena
   uint32_t epoch = 0;
   std::string key;  // shape of the captured graph
   hipGraphExec_t exec = nullptr;
@@ -1052,6 +1052,10 @@ static rs_status run_batch_eval(BatchWorkspace& W, const rs_graph* const* graphs
   const void* before[10] = {W.qs.p,  W.units.p, W.ubegin.p, W.per_query.p, W.parena.p,
                             W.agg.p, W.incl.p,  W.out.p,    W.ref.p,       W.cov.p};
   const uint64_t rec_bytes = 1024 * P.records;
+  // rows of the coefficient form that leave no room for the records
+  if (slot_budget && W.parena.bytes > P.parena_bytes &&
+      W.parena.bytes + std::max(W.agg.bytes, rec_bytes) + std::max(W.incl.bytes, rec_bytes) > slot_budget)
+    W.parena.release();
   if (W.per_query.reserve(P.per_query_bytes, st, false) || W.qs.reserve(sizeof(BQuery) * P.qs.size(), st, false) ||
       W.units.reserve(sizeof(MUnit) * std::max<size_t>(P.units.size(), 1), st, false) ||
       W.ubegin.reserve(4 * std::max<size_t>(P.ubegin.size(), 1), st, false) ||
@@ -1187,9 +1191,16 @@ rs_status run_batch_impl(const rs_graph* const* graphs, const rs_query* queries,
   }
   RS_HIP(hipEventRecord(W.ev0, st));
   {
+    // Both forms use the same two buffers in turn, so that a call holds the larger
+    // of the two and not their sum; the evaluation form's records are kept beside
+    // them and count against the budget.
     ProfScope ps(KC_BATCH, st, 0.0);
-    RS_TRY(run_coef_batch(*W.coef, graphs, plans, coef, results, st, slot_budget ? slot_budget : default_slot_budget(),
-                          &rest));
+    const uint64_t records = std::min(W.agg.bytes + W.incl.bytes, slot_budget);
+    const void* const before[2] = {W.per_query.p, W.parena.p};
+    const rs_status s = run_coef_batch(*W.coef, W.per_query, W.parena, graphs, plans, coef, results, st,
+                                       slot_budget ? slot_budget - records : default_slot_budget(), &rest);
+    if (before[0] != W.per_query.p || before[1] != W.parena.p) W.drop_graph();
+    RS_TRY(s);
   }
   RS_HIP(hipEventRecord(W.ev1, st));
   RS_HIP(hipEventSynchronize(W.ev1));

@@ -115,15 +115,22 @@ bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp);
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,
                            hipStream_t st, uint32_t* n_sums);
 
+// Device bytes of the setup and lists that run_coef reserves in ws.lists for this
+// plan or a part of its range (0: the plan runs in the evaluation form only).
+uint64_t coef_list_bytes(const rs_graph* g, const QueryPlan& qp, uint64_t eval_lists);
+
 // Many queries at once: each level is one launch over all of them (per class of
 // row widths). idx: the positions in graphs / plans / results to run. Queries
-// whose rows do not fit `budget` bytes are appended to *left and not run.
-struct CoefBatch;  // its device memory, kept between calls
+// whose rows do not fit `budget` bytes are appended to *left and not run. setup
+// and rows are the caller's, who uses them for other things between calls.
+struct CoefBatch;  // its descriptors, kept between calls
+// Device bytes of one query in a batch, without its rows.
+uint64_t coef_batch_query_bytes(const rs_graph* g, const QueryPlan& qp);
 CoefBatch* coef_batch_create();
 void coef_batch_destroy(CoefBatch* b);
 void coef_batch_release(CoefBatch* b);
 uint64_t coef_batch_bytes(const CoefBatch* b);
-rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std::vector<QueryPlan>& plans,
+rs_status run_coef_batch(CoefBatch& B, DevBuf& setup, DevBuf& rows, const rs_graph* const* graphs, const std::vector<QueryPlan>& plans,
                          const std::vector<uint32_t>& idx, rs_result* results, hipStream_t st, uint64_t budget,
                          std::vector<uint32_t>* left);
 

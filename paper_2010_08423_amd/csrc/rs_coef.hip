@@ -1883,6 +1883,30 @@ static bool dense_sets(const CoefQuery& q, const uint32_t* cnt, uint64_t span) {
   return q.m * span >= 100000000ull && 2 * total > (uint64_t)q.m * (q.k - 1);
 }
 
+// Whether run_coef may take this much for the setup and lists (see there).
+static bool setup_fits(uint64_t setup, uint64_t eval_lists) { return setup <= std::max<uint64_t>(eval_lists, 8 << 20); }
+
+uint64_t coef_list_bytes(const rs_graph* g, const QueryPlan& qp, uint64_t eval_lists) {
+  uint64_t most = 0;
+  if (!iter_rows_apply(qp)) return 0;
+  for (const uint64_t iters : {uint64_t(0), qp.it_end - qp.it_begin}) {
+    CoefQuery q{};
+    CoefShades sh{};
+    fill_query(q, sh, g->g, qp, nullptr, EdgeFilter(), false, kScanWaves);
+    q.iters = (uint32_t)iters;
+    const uint64_t b = carve_setup(q, sh, nullptr);
+    if (setup_fits(b, eval_lists)) most = std::max(most, b);
+  }
+  return most;
+}
+uint64_t coef_batch_query_bytes(const rs_graph* g, const QueryPlan& qp) {
+  if (qp.k < 3 || !coef_applies(qp)) return 0;
+  CoefQuery q{};
+  CoefShades sh{};
+  fill_query(q, sh, g->g, qp, nullptr, EdgeFilter(), false, kScanWaves);
+  return up(8ull * q.n * q.kq, 256) + up(carve_setup(q, sh, nullptr), 256) + sizeof(CoefQuery) + sizeof(CoefShades) + 256;
+}
+
 rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const QueryPlan& qp, const QueryExtras* ex,
                    const uint32_t* dv, const EdgeFilter& filt, uint64_t* T, hipStream_t st, bool timed,
                    std::vector<uint64_t>* sums_host, uint32_t* n_sums, bool by_iteration) {
@@ -1926,7 +1950,7 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
   // the rows that of its prefix state: a workspace sized for the evaluation
   // form holds the coefficient form too (small graphs: a few MB over).
   const uint64_t setup_bytes = carve_setup(q, a.sh, nullptr);
-  if (!ws.scratch && setup_bytes > std::max<uint64_t>(sz.lists, 8 << 20)) return RS_OK;
+  if (!ws.scratch && !setup_fits(setup_bytes, sz.lists)) return RS_OK;
   uint32_t cnt[kCoefMaxK - 1];
   for (uint32_t y = 0; y + 1 < k; ++y) cnt[y] = (uint32_t)m;
   uint64_t p_bytes, q_bytes;
@@ -2052,15 +2076,13 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
 // Many queries at once.
 // ---------------------------------------------------------------------------
 struct CoefBatch {
-  DevBuf desc, setup, rows;
+  DevBuf desc;
   uint8_t* host = nullptr;  // pinned: descriptors to upload, set sizes and results read back
   uint64_t host_bytes = 0;
 };
 CoefBatch* coef_batch_create() { return new CoefBatch(); }
 void coef_batch_release(CoefBatch* b) {
   b->desc.release();
-  b->setup.release();
-  b->rows.release();
   if (b->host) (void)hipHostFree(b->host);
   b->host = nullptr;
   b->host_bytes = 0;
@@ -2069,14 +2091,14 @@ void coef_batch_destroy(CoefBatch* b) {
   coef_batch_release(b);
   delete b;
 }
-uint64_t coef_batch_bytes(const CoefBatch* b) { return b->desc.bytes + b->setup.bytes + b->rows.bytes; }
+uint64_t coef_batch_bytes(const CoefBatch* b) { return b->desc.bytes; }
 
 // Queries of one launch share its LDS size, which follows the widest row; a row
 // product of k = 12 holds 61 KB per block, one of k = 9 13 KB, so the widths
 // are kept apart in these classes.
 static uint32_t width_class(uint32_t k) { return k <= 9 ? 0 : (k <= 11 ? 1 : 2); }
 
-rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std::vector<QueryPlan>& plans,
+rs_status run_coef_batch(CoefBatch& B, DevBuf& setup, DevBuf& rows, const rs_graph* const* graphs, const std::vector<QueryPlan>& plans,
                          const std::vector<uint32_t>& idx_in, rs_result* results, hipStream_t st, uint64_t budget,
                          std::vector<uint32_t>* left) {
   std::vector<uint32_t> idx = idx_in;
@@ -2119,16 +2141,16 @@ rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std:
     s_off[i] = setup_bytes;
     setup_bytes += up(carve_setup(qs[i], sh[i], nullptr), 256);
   }
-  if (B.setup.reserve(setup_bytes, st, false)) return RS_ENOMEM;
+  if (setup.reserve(setup_bytes, st, false)) return RS_ENOMEM;
   uint32_t* d_cnt = reinterpret_cast<uint32_t*>(dd + b_desc + b_sh);
   uint64_t* d_out = reinterpret_cast<uint64_t*>(dd + b_desc + b_sh + b_cnt);
   CoefGrid all;
   for (uint32_t i = 0; i < nq; ++i) {
     CoefQuery& q = qs[i];
-    q.z = reinterpret_cast<uint64_t*>(B.setup.as<uint8_t>() + z_off[i]);
+    q.z = reinterpret_cast<uint64_t*>(setup.as<uint8_t>() + z_off[i]);
     q.z1 = q.z;
     q.z1_stride = q.kq;
-    carve_setup(q, sh[i], B.setup.as<uint8_t>() + s_off[i]);
+    carve_setup(q, sh[i], setup.as<uint8_t>() + s_off[i]);
     q.count = d_cnt + 16 * i;
     q.det = d_out + i;
     q.result = res + (uint64_t)top_cap * i;
@@ -2179,11 +2201,11 @@ rs_status run_coef_batch(CoefBatch& B, const rs_graph* const* graphs, const std:
     most = std::max(most, at);
   }
   rounds.push_back({first, nq});
-  if (B.rows.reserve(most > B.rows.bytes ? std::min(std::max(budget, most), most + most / 8) : 8, st, false))
+  if (rows.reserve(most > rows.bytes ? std::min(std::max(budget, most), most + most / 8) : 8, st, false))
     return RS_ENOMEM;
   for (uint32_t i = 0; i < nq; ++i) {
-    qs[i].P = reinterpret_cast<uint64_t*>(B.rows.as<uint8_t>() + p_off[i]);
-    qs[i].Q = reinterpret_cast<uint64_t*>(B.rows.as<uint8_t>() + q_off[i]);
+    qs[i].P = reinterpret_cast<uint64_t*>(rows.as<uint8_t>() + p_off[i]);
+    qs[i].Q = reinterpret_cast<uint64_t*>(rows.as<uint8_t>() + q_off[i]);
     if (!run[i]) qs[i].k = 0;  // (no kernel takes a query of no levels)
   }
   RS_HIP(hipMemcpyAsync(dd, B.host, b_desc + b_sh, hipMemcpyHostToDevice, st));

@@ -34,6 +34,7 @@
 #include <thread>
 #include <vector>
 
+#include "rs_coef.h"
 #include "rs_internal.h"
 
 namespace rs {
@@ -219,7 +220,7 @@ static bool take_job(rs_server* S, Job& job) {
     // a group: small-graph queries in arrival order while work, slots and
     // memory allow, each with all its remaining iterations or a slice of them
     const uint64_t slot_share = S->budget / 4;  // prefix-state arena of the group's rounds
-    uint64_t work = 0, bytes = slot_share;
+    uint64_t work = 0, bytes = slot_share + (1 << 20);  // (and the run bounds of its launches)
     const uint64_t slots = S->opts.max_inflight - S->inflight;
     std::vector<size_t> pick;     // queue positions, ascending
     std::vector<uint64_t> ends;   // iterations each picked query runs up to
@@ -458,7 +459,18 @@ rs_status rs_server_submit(rs_server* s, uint32_t graph_id, const rs_query* q, u
       s->st.rejected++;
       return RS_ENOMEM;
     }
-    a->group_bytes = batch_query_bytes(m, n, a->plan);
+    // The coefficient form's lists may be a few MB larger than the evaluation form's
+    // (small graphs); a budget without room for them leaves the query to the latter.
+    const uint64_t lists = coef_list_bytes(g, a->plan, a->sizes.lists);
+    const uint64_t more = (lists > a->sizes.lists ? lists - a->sizes.lists : 0) + 64;
+    if (a->sizes.total() + more <= s->budget)
+      a->sizes.lists += more;
+    else
+      a->tu.eval_form = true;
+    // in a group: either form's tables, a few words per edge and vertex that a round
+    // shares, and its units
+    a->group_bytes = std::max(batch_query_bytes(m, n, a->plan), coef_batch_query_bytes(g, a->plan)) + 6 * (m + n) + 4096 +
+                     1024 * (a->plan.chunk_last - a->plan.chunk_first);
     a->ticket = s->next_ticket++;
     a->graph_id = graph_id;
     a->q = *q;

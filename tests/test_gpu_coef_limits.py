@@ -181,3 +181,48 @@ def test_outputs_of_both_readings_share_a_buffer():
     for _ in range(2):
         for want, got in ((fine, R.run_fine(gd, 4, 6, 5)), (lit, R.run_literal(gd, 4, 6, 5))):
             assert np.array_equal(got.zeta, want[0]) and np.array_equal(got.reach, want[1])
+
+
+def serve(srv, gid, queries):
+    tickets = [srv.submit(gid, q) for q in queries]
+    return [srv.poll(t, wait_ms=100_000).fingerprint for t in tickets]
+
+
+def test_server_stays_in_its_budget():
+    """Groups of whole queries (coefficient form, rows in several rounds), of
+    parts of ranges (evaluation form) and of both, one after another: what the
+    server takes of the device's memory stays within the budget."""
+    import threading
+
+    import torch
+
+    g = inputs.uniform_graph(10_000, 100_000, 200, seed=3)
+    gd = R.Graph.from_inputs(g)
+    whole = [inputs.Query(k=8, delta=60, seed=i) for i in range(18)]
+    parts = [inputs.Query(k=8, delta=60, seed=i, it_begin=0, it_end=200) for i in range(18)]
+    want = {id(q): R.run(gd, q.k, q.delta, q.seed, it_begin=q.it_begin, it_end=q.it_end).fingerprint for q in whole + parts}
+    budget, slack = 2 << 30, 64 << 20
+    free0 = torch.cuda.mem_get_info()[0]
+    least, stop = [free0], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            least[0] = min(least[0], torch.cuda.mem_get_info()[0])
+            stop.wait(0.0005)
+
+    th = threading.Thread(target=watch)
+    th.start()
+    try:
+        srv = R.Server(hbm_budget=budget, streams=1)
+        gid = srv.add_graph(gd)
+        mixed = [q for pair in zip(whole[:9], parts[:9]) for q in pair]
+        for queries in (whole, parts, mixed, whole, parts):
+            say("[server] budget: group of", len(queries), "first range", queries[0].it_end, queries[1].it_end)
+            assert serve(srv, gid, queries) == [want[id(q)] for q in queries]
+        assert srv.stats()["held_bytes"] <= budget
+        srv.close()
+    finally:
+        stop.set()
+        th.join()
+    say("[server] budget", budget, "taken", free0 - least[0])
+    assert free0 - least[0] <= budget + slack
