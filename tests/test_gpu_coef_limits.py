@@ -226,3 +226,40 @@ def test_server_stays_in_its_budget():
         th.join()
     say("[server] budget", budget, "taken", free0 - least[0])
     assert free0 - least[0] <= budget + slack
+
+
+def test_batch_leaves_queries_with_too_large_rows():
+    """A small budget: the rows of k = 12 exceed a group's share and the queries run
+    in the evaluation form, next to others that fit it a few at a time."""
+    g = inputs.uniform_graph(600, 12_000, 40, seed=4)
+    gd = R.Graph.from_inputs(g)
+    queries = [inputs.Query(k=k, delta=30, seed=10 * k + i) for i in range(3) for k in (12, 5, 9, 7)]
+    want = [R.run(gd, q.k, q.delta, q.seed).fingerprint for q in queries]
+    need = max(R.footprint(gd, q.k, q.delta) for q in queries)
+    for budget in (need + (32 << 20), 4 * need, 4 << 30):
+        srv = R.Server(hbm_budget=budget, streams=1)
+        gid = srv.add_graph(gd)
+        say("[server] rows beyond the share, budget", budget)
+        assert serve(srv, gid, queries) == want
+        srv.close()
+
+
+def test_tuned_shapes_give_the_same_results():
+    """The launch shapes that the tuner picks belong to the evaluation form, which
+    default calls leave to larger k: given as knobs, they run."""
+    g = inputs.add_colours(inputs.chung_lu_graph(800, 9000, 2.3, 60, seed=8), 4, seed=8)
+    gd = R.Graph.from_inputs(g)
+    queries = [inputs.Query(k=k, delta=4, seed=k, motif=None if k % 2 else np.array([1, 1, 2, k - 4], np.uint8)) for k in range(5, 9)]
+    want = [oracle.sieve(g.n, g.src, g.dst, g.t, q.k, q.delta, q.seed, threads=host_threads(),
+                         **(dict(colour=g.colour, n_colours=4, motif=q.motif) if q.motif is not None else {})) for q in queries]
+    for tuned in (R.autotune(gd, queries), R.autotune_batch(gd, queries)):
+        assert tuned.edges_per_tile in (8, 16) and tuned.waves_per_block in (1, 2, 4)
+        for q, F in zip(queries, want):
+            r = R.run(gd, q.k, q.delta, q.seed, motif=q.motif, tuning=tuned, per_iteration=True)
+            assert r.fingerprint == F == int(np.bitwise_xor.reduce(r.per_iteration))
+        assert [r.fingerprint for r in R.run_batch([gd] * 4, queries, tuning=tuned)[0]] == want
+        half = [inputs.Query(k=q.k, delta=q.delta, seed=q.seed, motif=q.motif, it_begin=0, it_end=1 << q.k - 1) for q in queries]
+        rest = [inputs.Query(k=q.k, delta=q.delta, seed=q.seed, motif=q.motif, it_begin=1 << q.k - 1, it_end=1 << q.k) for q in queries]
+        # (parts of the range run in the evaluation form with the graph's tuned batch shape)
+        parts = [r.fingerprint for r in R.run_batch([gd] * 8, half + rest)[0]]
+        assert [a ^ b for a, b in zip(parts[:4], parts[4:])] == want
