@@ -1013,10 +1013,11 @@ static uint64_t default_slot_budget() {
 constexpr uint64_t kRoundStateBytes = 20ull << 30;
 
 // slot_budget: bytes of prefix state the call may hold over all its stream
-// lanes (0 = a third of free device memory).
+// lanes (0 = a third of free device memory). *ran: the status returned is that of
+// single queries, and every other query has its result.
 static rs_status run_batch_eval(BatchWorkspace& W, const rs_graph* const* graphs, const rs_query* queries, uint32_t nq,
                                 rs_result* results, const rs_tuning* tune, hipStream_t st, bool use_graph,
-                                uint64_t slot_budget) {
+                                uint64_t slot_budget, bool* ran = nullptr) {
   // launch shape: explicit knobs, else the graph's autotuned batch shape, else defaults
   Tuning tu;
   tu.top_edges_per_tile = 128;
@@ -1047,6 +1048,7 @@ static rs_status run_batch_eval(BatchWorkspace& W, const rs_graph* const* graphs
   rs_status first_err = RS_OK;
   for (uint32_t i = 0; i < nq; ++i)
     if (results[i].status != RS_OK && first_err == RS_OK) first_err = results[i].status;
+  if (ran) *ran = P.qs.empty();
   if (P.qs.empty()) return first_err;
   // device memory; a reallocation invalidates the captured graph
   const void* before[10] = {W.qs.p,  W.units.p, W.ubegin.p, W.per_query.p, W.parena.p,
@@ -1156,6 +1158,7 @@ static rs_status run_batch_eval(BatchWorkspace& W, const rs_graph* const* graphs
     r.status = RS_OK;
   }
   for (uint32_t i = 0; i < nq; ++i) results[i].device_ms = ms;
+  if (ran) *ran = true;
   return first_err;
 }
 
@@ -1216,15 +1219,17 @@ rs_status run_batch_impl(const rs_graph* const* graphs, const rs_query* queries,
       gl.push_back(graphs[i]);
       ql.push_back(queries[i]);
     }
+    bool ran = false;
     const rs_status s = run_batch_eval(W, gl.data(), ql.data(), (uint32_t)rest.size(), rl.data(), tune, st, use_graph,
-                                       slot_budget);
+                                       slot_budget, &ran);
     float more = 0;
     for (size_t j = 0; j < rest.size(); ++j) {
+      if (!ran && rl[j].status == RS_OK) rl[j].status = s;  // without its result
       results[rest[j]] = rl[j];
       more = std::max(more, rl[j].device_ms);
     }
     ms += more;
-    if (s != RS_OK && std::all_of(rl.begin(), rl.end(), [](const rs_result& r) { return r.status == RS_OK; })) return s;
+    if (!ran) return s;
   }
   rs_status first_err = RS_OK;
   for (uint32_t i = 0; i < nq; ++i) {

@@ -263,3 +263,18 @@ def test_tuned_shapes_give_the_same_results():
         # (parts of the range run in the evaluation form with the graph's tuned batch shape)
         parts = [r.fingerprint for r in R.run_batch([gd] * 8, half + rest)[0]]
         assert [a ^ b for a, b in zip(parts[:4], parts[4:])] == want
+
+
+def test_batch_that_runs_out_of_memory_says_so():
+    """Queries of the evaluation form whose tables exceed the device's memory, next to
+    an invalid one: the call's error and theirs, not a result of zero."""
+    gd = R.Graph.from_inputs(inputs.uniform_graph(100_000, 1_000_000, 1000, seed=4))
+    queries = [inputs.Query(k=5, delta=3, seed=1), inputs.Query(k=1, delta=3, seed=2)]
+    queries += [inputs.Query(k=16, delta=3, seed=i) for i in range(200)]  # 2.2 GB of tables each
+    res, st = R.run_batch([gd] * len(queries), queries)
+    assert st == R.RS_ENOMEM and res[1].status == R.RS_EINVAL
+    assert all(r.status == R.RS_ENOMEM for r in res[2:])
+    assert res[0].status == R.RS_OK and res[0].fingerprint == R.run(gd, 5, 3, 1).fingerprint
+    # the workspace is as good as before
+    res, st = R.run_batch([gd] * 2, [queries[0], inputs.Query(k=5, delta=3, seed=1, it_begin=0, it_end=32)])
+    assert st == R.RS_OK and res[0].fingerprint == res[1].fingerprint != 0
