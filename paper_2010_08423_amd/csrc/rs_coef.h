@@ -27,8 +27,10 @@ constexpr uint32_t kForwardLevels = 6;
 // past them.
 __host__ __device__ inline uint64_t flag_stride(uint64_t words) { return words * 64 + 64; }
 
-// Bytes of one level's window marks: one per edge, one per block of edges.
-__host__ __device__ inline uint64_t mark_stride(uint64_t blocks) { return blocks * kSetBlock + ((blocks + 7) & ~7ull); }
+// Bytes of one level's window marks: one per edge, one per block of edges. The
+// backward pass reads them 16 at a time.
+__host__ __device__ constexpr uint64_t mark_stride(uint64_t blocks) { return blocks * kSetBlock + ((blocks + 15) & ~15ull); }
+static_assert(mark_stride(4) % 16 == 0 && mark_stride(20) % 16 == 0, "each level's marks start on 16 bytes");
 
 // One query in the coefficient form: its graph, constraints and buffers.
 struct CoefQuery {
