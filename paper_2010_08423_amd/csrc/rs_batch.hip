@@ -1200,8 +1200,11 @@ rs_status run_batch_impl(const rs_graph* const* graphs, const rs_query* queries,
     ProfScope ps(KC_BATCH, st, 0.0);
     const uint64_t records = std::min(W.agg.bytes + W.incl.bytes, slot_budget);
     const void* const before[2] = {W.per_query.p, W.parena.p};
-    const rs_status s = run_coef_batch(*W.coef, W.per_query, W.parena, graphs, plans, coef, results, st,
-                                       slot_budget ? slot_budget - records : default_slot_budget(), &rest);
+    rs_status s = RS_OK;
+    for (size_t i = 0; s == RS_OK && i < coef.size(); i += kCoefQueries)
+      s = run_coef_batch(*W.coef, W.per_query, W.parena, graphs, plans,
+                         std::vector<uint32_t>(coef.begin() + i, coef.begin() + std::min(coef.size(), i + kCoefQueries)),
+                         results, st, slot_budget ? slot_budget - records : default_slot_budget(), &rest);
     if (before[0] != W.per_query.p || before[1] != W.parena.p) W.drop_graph();
     RS_TRY(s);
   }

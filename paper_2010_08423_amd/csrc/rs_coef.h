@@ -125,6 +125,9 @@ uint64_t coef_list_bytes(const rs_graph* g, const QueryPlan& qp, uint64_t eval_l
 // row widths). idx: the positions in graphs / plans / results to run. Queries
 // whose rows do not fit `budget` bytes are appended to *left and not run. setup
 // and rows are the caller's, who uses them for other things between calls.
+// A launch has a grid slice per query, along y or z, where it takes 65536: calls
+// run at most kCoefQueries at once.
+constexpr size_t kCoefQueries = 32768;
 struct CoefBatch;  // its descriptors, kept between calls
 // Device bytes of one query in a batch, without its rows.
 uint64_t coef_batch_query_bytes(const rs_graph* g, const QueryPlan& qp);

@@ -278,3 +278,12 @@ def test_batch_that_runs_out_of_memory_says_so():
     # the workspace is as good as before
     res, st = R.run_batch([gd] * 2, [queries[0], inputs.Query(k=5, delta=3, seed=1, it_begin=0, it_end=32)])
     assert st == R.RS_OK and res[0].fingerprint == res[1].fingerprint != 0
+
+
+def test_batch_of_more_queries_than_a_grid_takes():
+    gd = R.Graph.from_inputs(inputs.uniform_graph(30, 200, 20, seed=4))
+    some = [inputs.Query(k=3 + i % 3, delta=1 + i % 5, seed=i) for i in range(40)]
+    want = [R.run(gd, q.k, q.delta, q.seed).fingerprint for q in some]
+    n = 66_000
+    res, st = R.run_batch([gd] * n, [some[i % 40] for i in range(n)])
+    assert st == R.RS_OK and [r.fingerprint for r in res] == [want[i % 40] for i in range(n)]
