@@ -103,8 +103,9 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
 
 // The literal reading of one query in the coefficient form: zeta per slot in
 // L.zs; the fingerprint is the XOR of *n_sums words of L.host_result once st is
-// synchronised. *n_sums = 0 (and RS_OK): its rows exceed kLitRows, only scratch
-// was written. A slot's row is formed by one wave, so graphs with more than
+// synchronised. *n_sums = 0 (and RS_OK): its rows exceed kLitRows or its buffers
+// the device's memory, only scratch was written. (It may need more than the
+// evaluation form: 16 bytes per edge and level against 1 KB per slot.) A slot's row is formed by one wave, so graphs with more than
 // kLitSlotEdges edges into one vertex at one time are left to the evaluation form,
 // which cuts slots into tiles. So are, up to k = 6, where that form takes a
 // single pass of 64 iterations, graphs whose slots all are long (6*10^4 edges, 25

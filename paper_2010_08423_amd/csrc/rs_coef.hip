@@ -2604,7 +2604,7 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
     c.take(T.te, lv * m);
     return c.off;
   };
-  if (L.coef.reserve(carve(nullptr), st, false)) return RS_ENOMEM;
+  if (L.coef.reserve(carve(nullptr), st, false)) return RS_OK;
   carve(L.coef.as<uint8_t>());
   T.zs = L.zs.as<uint64_t>();
   if (!L.host_result) RS_HIP(hipHostMalloc((void**)&L.host_result, 8 * kTopBlocks, hipHostMallocDefault));
@@ -2624,7 +2624,7 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
   uint64_t rows = 256;  // two buffers in turn
   for (uint32_t l = 2; l < k; ++l) rows = std::max<uint64_t>(rows, 8ull * cnt[l - 2] * binom(k, l));
   if (2 * rows > kLitRows) return RS_OK;
-  if (L.chi0.reserve(rows, st, false) || L.chi1.reserve(rows, st, false)) return RS_ENOMEM;
+  if (L.chi0.reserve(rows, st, false) || L.chi1.reserve(rows, st, false)) return RS_OK;
   ProfScope ps(KC_LITERAL, st, 0.0);
   hipLaunchKernelGGL(k_litc_lists, dim3(q.blocks + T.nbe, k - 1), dim3(256), 0, st, a, T);
   RS_HIP(hipGetLastError());

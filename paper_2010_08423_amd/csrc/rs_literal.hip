@@ -553,7 +553,14 @@ static rs_status run_literal(rs_graph* g, const QueryPlan& qp, const uint32_t* d
   // The coefficient form where it applies (rs_coef.hip: whole ranges, 3 <= k <= 12)
   uint32_t n_sums = 0;
   if (lit_coef_applies(L, m, qp)) RS_TRY(run_literal_coef(G, L, qp, dv, hp, st, &n_sums));
-  if (!n_sums) RS_TRY(run_literal_eval(G, L, qp, dv, hp, st));
+  if (!n_sums) {
+    rs_status s = run_literal_eval(G, L, qp, dv, hp, st);
+    if (s == RS_ENOMEM && L.coef.p) {  // what the coefficient form holds may be what is missing
+      L.coef.release();
+      s = run_literal_eval(G, L, qp, dv, hp, st);
+    }
+    RS_TRY(s);
+  }
   RS_HIP(launch_fill32(L.reach.as<uint32_t>(), 0xFFFFFFFFu, n, st));
   uint64_t F = 0;
   if (!n_sums) RS_HIP(hipMemcpyAsync(&F, L.out.p, 8, hipMemcpyDeviceToHost, st));

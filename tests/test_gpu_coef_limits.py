@@ -287,3 +287,33 @@ def test_batch_of_more_queries_than_a_grid_takes():
     n = 66_000
     res, st = R.run_batch([gd] * n, [some[i % 40] for i in range(n)])
     assert st == R.RS_OK and [r.fingerprint for r in res] == [want[i % 40] for i in range(n)]
+
+
+def test_literal_with_little_memory_left():
+    """Slots of 100 edges: the coefficient form's tables (16 bytes per edge and level)
+    take more than the evaluation form, which runs where only that fits."""
+    import torch
+
+    n, dsts, times, per = 3001, 400, 100, 100
+    s = np.arange(dsts * times)
+    src = ((s[:, None] * 37 + np.arange(per) * 29) % n).astype(np.uint32).ravel()
+    dst = np.repeat(s % dsts, per).astype(np.uint32)
+    t = np.repeat(1 + s // dsts, per).astype(np.uint32)
+    args = (12, 1, 5)
+    want = R.run_literal(R.Graph(n, src, dst, t), *args)
+    gd = R.Graph(n, src, dst, t)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    leave = 1000 << 20
+    hold = []
+    try:
+        while torch.cuda.mem_get_info()[0] > leave + (8 << 20):
+            hold.append(torch.empty(torch.cuda.mem_get_info()[0] - leave, dtype=torch.uint8, device="cuda"))
+        say("[coef] literal, free", torch.cuda.mem_get_info()[0])
+        for _ in range(2):
+            got = R.run_literal(gd, *args)
+            assert np.array_equal(got.zeta, want.zeta) and np.array_equal(got.reach, want.reach)
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    assert R.run_literal(gd, *args).fingerprint == want.fingerprint
