@@ -444,7 +444,7 @@ __global__ __launch_bounds__(1024) void k_coef_fwd(A arg, uint32_t l) {
 // past the block's end it is looked up once per block.
 //
 // R: set blocks per thread block. An edge's work is a chain of four dependent
-// loads, so on graphs that fill the GPU anyway a thread takes four edges with
+// loads, so on graphs that fill the GPU anyway (kWideSets) a thread takes four edges with
 // their loads in flight together (4*10^6 edges: 30 us per level with one edge
 // per thread, 20 with four); on small graphs one edge per thread finishes
 // earlier.
@@ -1626,8 +1626,11 @@ constexpr uint32_t kScanWaves = 4096;
 constexpr uint32_t kTopBlocks = 1024;
 // Blocks of the row products that go over a list in turn.
 constexpr uint32_t kMulBlocks = 2048;
-// Edges from which a thread of the backward pass takes four.
-constexpr uint64_t kWideSets = 600000;
+// Edges from which a thread of the backward pass takes four. (k = 8, Chung-Lu and
+// uniform graphs, one edge per thread against four, us per query: 6*10^5 edges 282
+// and 297, 219 and 231; 10^6 365 and 373, 237 and 241; 2*10^6 628 and 609, 354 and 336;
+// 4*10^6 1076 and 1046, 545 and 508.)
+constexpr uint64_t kWideSets = 1400000;
 // Entries per run from which the carries get a launch of their own.
 constexpr uint64_t kLongRun = 32;
 // Runs that one destination may span from which the carries come from prefix

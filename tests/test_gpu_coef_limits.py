@@ -42,9 +42,9 @@ def hub_graph(arrivals, leave, feeders=2000):
 
 
 # The search for the next marked window end goes on past 64 blocks of 1024
-# edges in steps of 1024 blocks: one step from some 10^5 arrivals on, with one
-# edge per thread and, from 600000 edges on, four; a second step from 1.12*10^6.
-@pytest.mark.parametrize("arrivals", [100_000, 400_000, 700_000, 1_300_000])
+# edges in steps of 1024 blocks: one step from some 10^5 arrivals on, a second one
+# from 1.12*10^6; with one edge per thread and, from 1.4*10^6 edges on, four.
+@pytest.mark.parametrize("arrivals", [100_000, 400_000, 700_000, 1_300_000, 1_500_000])
 def test_next_window_end_far_past_a_block(arrivals):
     for leave in ((1.0,), (0.3, 0.97)):
         g, last = hub_graph(arrivals, leave)
@@ -317,3 +317,19 @@ def test_literal_with_little_memory_left():
         del hold
         torch.cuda.empty_cache()
     assert R.run_literal(gd, *args).fingerprint == want.fingerprint
+
+
+# Backward passes with one and with four edges per thread; at 2.6*10^6 edges the
+# rows are sized from the set sizes, and long runs leave their carries to a launch
+# of their own.
+@pytest.mark.parametrize("m,k,delta", [(1_399_999, 4, 60), (1_400_001, 5, 60), (2_600_000, 8, 60)])
+def test_large_graphs(m, k, delta):
+    g = inputs.add_colours(inputs.chung_lu_graph(m // 10, m, 2.5, 1000, seed=k), 4, seed=k)
+    gd = R.Graph.from_inputs(g)
+    for motif in (None, np.array([1, 1, 1, k - 3], np.uint8)):
+        say("[coef] large m", m, "k", k, "motif", motif is not None)
+        e = R.run(gd, k, delta, 3, motif=motif, per_iteration=True, tuning=R.Tuning(edges_per_tile=16))
+        assert R.run(gd, k, delta, 3, motif=motif).fingerprint == e.fingerprint
+        for lo, hi in ((0, 1 << k), (3, 9)):
+            r = R.run(gd, k, delta, 3, motif=motif, it_begin=lo, it_end=hi, per_iteration=True)
+            assert np.array_equal(r.per_iteration, e.per_iteration[lo:hi])
