@@ -148,8 +148,9 @@ typedef struct {
 /* Launch-shape knobs; zero fields mean "choose automatically". They shape the
  * evaluation form (all 2^k iterations of a range, 64 per wavefront): a call that
  * sets one of edges_per_tile, top_edges_per_tile, chunks_per_launch,
- * waves_per_block and chunks_per_wave runs in it, and so does a batch that gives
- * any tuning with one of them. Without them, queries with k <= 12 run in the
+ * waves_per_block and chunks_per_wave runs in it, and so does a batch with any
+ * non-zero field, max_slots and no_graph included (its rounds and its captured
+ * graph are that form's). Without them, queries with k <= 12 run in the
  * coefficient form (C(k,l) values per slot of level l, or, for single iterations
  * and parts of the range, one per iteration) where its buffers fit; results are
  * identical. */
@@ -298,7 +299,12 @@ rs_status rs_extract(const rs_graph* g, const rs_query* q, const rs_constraints*
  * XOR of the slot values (a checksum, not a decision value). delta_per_vertex:
  * host array of n resting times or NULL for q->delta. The iteration range of
  * q selects the iterations summed. The graph's slot structure is built on the
- * first call (4 bytes per edge and per slot, kept with the graph). */
+ * first call (4 bytes per edge and per slot) and kept with the graph, as are the
+ * query's buffers: for whole ranges with 3 <= k <= 12 some 16 bytes per edge and
+ * 24 per slot and level and up to 16 GiB of rows (graphs with more than 128
+ * edges into a vertex at one time, or without that much memory, do without them),
+ * else 16 bytes per edge and up to 8 GiB of slot states. slot_zeta passes through
+ * the pinned buffer of rs_run_fine. */
 rs_status rs_run_literal(const rs_graph* g, const rs_query* q, const uint32_t* delta_per_vertex,
                          uint32_t* reach_time, uint64_t* slot_zeta, rs_result* r, void* hip_stream);
 
@@ -321,7 +327,16 @@ rs_status rs_run_noalloc(const rs_graph* g, const rs_query* q, uint64_t* per_ite
                          void* hip_stream);
 
 /* Batched path: nq queries, each on its own graph (graphs[i]; graphs may
- * repeat), evaluated together. Every (query, 64-iteration chunk) is a unit
+ * repeat), evaluated together.
+ *
+ * Without tuning, queries over whole iteration ranges with 3 <= k <= 12 run in the
+ * coefficient form: each set pass and each level is one launch over all of them
+ * (at most 32768 at once, and as many at a level as have rows within a third of
+ * free device memory). The call synchronises once on the way, to read the set
+ * sizes. Parts of a range, k = 2, k > 12, queries whose rows alone exceed that
+ * memory, and every query of a call with tuning run in the evaluation form:
+ *
+ * Every (query, 64-iteration chunk) is a unit
  * with its own prefix-state buffers; units are packed into rounds, and four
  * stream lanes run one round each at a time. A round holds at most max_slots
  * units and at most a quarter of the HBM budget (a third of free device
@@ -331,7 +346,9 @@ rs_status rs_run_noalloc(const rs_graph* g, const rs_query* q, uint64_t* per_ite
  * sequence is captured once per batch shape into a hipGraph and replayed with
  * new descriptors (tune->no_graph = 1 enqueues it directly).
  * results[i].status holds each query's status (RS_EINVAL for an invalid
- * query, which is skipped); the call returns the first error, or RS_OK.
+ * query, which is skipped); the call returns the first error, or RS_OK. Where
+ * a part of the batch fails as a whole, that error is returned, and queries whose
+ * status is RS_OK may be without their result.
  * tune == NULL uses the shape rs_autotune chose for graphs[0] (or a default).
  * Results are bit-identical to rs_run. Calls are serialised internally. */
 rs_status rs_run_batch(const rs_graph* const* graphs, const rs_query* queries, uint32_t nq,
@@ -339,7 +356,9 @@ rs_status rs_run_batch(const rs_graph* const* graphs, const rs_query* queries, u
 
 /* Times candidate launch shapes on the sample queries and returns the
  * fastest; the choice is cached per (graph, k class) for later NULL-tuning
- * calls. */
+ * calls. The shapes are the evaluation form's (see rs_tuning): they apply to
+ * later calls that run in it, k > 12 for instance, and to calls that pass them
+ * as knobs; default calls with k <= 12 stay in the coefficient form. */
 rs_status rs_autotune(const rs_graph* g, const rs_query* sample, uint32_t ns, rs_tuning* out);
 
 /* Batched path only: times candidate batched launch shapes (edges per tile,

@@ -92,8 +92,8 @@ bool coef_applies(const QueryPlan& qp);
 bool iter_rows_apply(const QueryPlan& qp);
 // Enqueues one query in the coefficient form on ws. *n_sums = 0 (and RS_OK)
 // when its rows do not fit what sz allows the evaluation form; only scratch was
-// written then. Constraint arrays are on the device already; T is the zeroed
-// per-edge sum array of a fine-grained query. Once the caller has synchronised
+// written then. Constraint arrays are on the device already; T is the per-edge sum
+// array of a fine-grained query, cleared or written whole here. Once the caller has synchronised
 // st, the fingerprint is the XOR of *n_sums words in ws.host_result, or, on a
 // workspace without it (no allocation), in *sums. by_iteration: the words are the
 // values of the plan's iterations in turn.
@@ -105,12 +105,14 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
 // L.zs; the fingerprint is the XOR of *n_sums words of L.host_result once st is
 // synchronised. *n_sums = 0 (and RS_OK): its rows exceed kLitRows or its buffers
 // the device's memory, only scratch was written. (It may need more than the
-// evaluation form: 16 bytes per edge and level against 1 KB per slot.) A slot's row is formed by one wave, so graphs with more than
-// kLitSlotEdges edges into one vertex at one time are left to the evaluation form,
-// which cuts slots into tiles. So are, up to k = 6, where that form takes a
-// single pass of 64 iterations, graphs whose slots all are long (6*10^4 edges, 25
-// per slot, delta = 5: k = 3, 395 us there and 414 here, k = 6, 653 and 679; k = 9,
-// 3185 and 1241. With 3 per slot and 90 at a hub, k = 3, 1571 and 1439).
+// evaluation form: 16 bytes per edge and level against 1 KB per slot.)
+//
+// A slot's row is formed by one wave, 64 coefficients and an edge at a time, so
+// graphs with more than kLitSlotEdges edges into one vertex at one time are left
+// to the evaluation form, which cuts slots into tiles, and so are shorter slots
+// whose chain is long against that form's work (lit_coef_applies) and, up to k = 6,
+// where that form takes one pass of 64 iterations, graphs with more than
+// kLitMeanEdges edges per slot.
 constexpr uint32_t kLitSlotEdges = 128;
 constexpr uint64_t kLitMeanEdges = 8;
 constexpr uint64_t kLitRows = 16ull << 30;  // what the evaluation form's two buffers may hold together

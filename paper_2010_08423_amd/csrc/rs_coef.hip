@@ -2097,8 +2097,8 @@ void coef_batch_destroy(CoefBatch* b) {
 uint64_t coef_batch_bytes(const CoefBatch* b) { return b->desc.bytes; }
 
 // Queries of one launch share its LDS size, which follows the widest row; a row
-// product of k = 12 holds 61 KB per block, one of k = 9 13 KB, so the widths
-// are kept apart in these classes.
+// product of k = 12 holds 61 KB per block (77 KB where it sums the carries itself),
+// one of k = 9 13 KB (16 KB), so the widths are kept apart in these classes.
 static uint32_t width_class(uint32_t k) { return k <= 9 ? 0 : (k <= 11 ? 1 : 2); }
 
 rs_status run_coef_batch(CoefBatch& B, DevBuf& setup, DevBuf& rows, const rs_graph* const* graphs, const std::vector<QueryPlan>& plans,
@@ -2562,8 +2562,18 @@ __global__ __launch_bounds__(256) void k_litc_top(OneCoef a, LitCoef T) {
 constexpr uint64_t kLitBlocks = 1 << 20;
 
 bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp) {
-  return qp.k >= 3 && coef_applies(qp) && L.ns && L.max_slot_edges <= kLitSlotEdges &&
-         (qp.k > 6 || m <= kLitMeanEdges * L.ns);
+  if (qp.k < 3 || !coef_applies(qp) || !L.ns || L.max_slot_edges > kLitSlotEdges) return false;
+  if (qp.k <= 6 && m > kLitMeanEdges * L.ns) return false;
+  // Edges that the longest slot's wave goes over, a pass per 64 coefficients, over
+  // the levels, and edges per wave of the evaluation form with 8192 waves at
+  // once. (Us there and here at a ratio of 2.2: 860 and 772, k = 7, 25 edges per slot;
+  // 2.7: 623 and 598; 3.6: 595 and 602; 4.8: 516 and 568; 6.5: 628 and 1935, k = 10,
+  // 2*10^4 edges. Up to k = 6 it is 1.4 to 2.3 for 6*10^4 edges, 25 per slot, k = 3, 395 and
+  // 414, k = 6, 653 and 679, and for 3 per slot and 90 at a hub, k = 3, 1571 and 1439.)
+  uint64_t passes = 0;
+  for (uint32_t l = 2; l < qp.k; ++l) passes += (binom(qp.k, l - 1) + 63) / 64;
+  const uint64_t eval = (qp.k - 1) * std::max<uint64_t>(kLiteralTile, m * (qp.chunk_last - qp.chunk_first) / 8192);
+  return 2 * L.max_slot_edges * passes <= 7 * eval;
 }
 
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,
