@@ -1738,18 +1738,21 @@ static uint32_t carried_levels(const CoefQuery& q, const CoefShades& sh, const u
 }
 // Levels where one destination may span more than kFarRuns runs. A list with
 // known size is taken to hold a vertex's arrivals at up to eight times the rate at
-// which it holds all edges; sizes that are only bounds (sized false) leave a run's
-// length open, and it is taken as one tile. (40000 of 50000 edges into one vertex,
-// k = 3: 308 us per query with the tails summed one by one, 98 with prefix sums;
-// 700000 of 10^6: 1846 and 214. A 4*10^6-edge motif query, 84000 arrivals at one
-// vertex, few of them in the lists: 1484 and 1527.)
+// which it holds all edges. Sizes that are only bounds (sized false) leave a run's
+// length open, and it is taken as one tile, on graphs with a sixteenth of all
+// arrivals at one vertex: with less, the tails one by one cost no more than the two
+// launches. (Us per query one by one and with prefix sums: 40000 of 50000 edges into
+// one vertex, k = 3, 308 and 98; 700000 of 10^6, 1846 and 214; 160000 of 8*10^5, most
+// others unused, k = 3, 376 and 153, k = 6, 250 and 213; 12000 of 6*10^4, k = 6, where a
+// list holds few of them, 110 and 140. Sized, 4*10^6-edge motif query, 84000 arrivals
+// at one vertex, few of them in the lists: 1484 and 1527.)
 static uint32_t far_levels(const CoefQuery& q, const CoefShades& sh, const uint32_t* cnt, bool sized, uint64_t m,
                            uint64_t most_arrivals) {
   uint32_t b = 0;
   for (uint32_t l = 2; l < q.k; ++l) {
     const uint64_t n = cnt[l - 2], runs = scan_runs(q, sh, n, l);
     const uint64_t span = sized ? std::min({n, most_arrivals, 8 * most_arrivals * n / m + 1}) * runs / std::max<uint64_t>(n, 1)
-                                : most_arrivals / kTile;
+                                : (16 * most_arrivals >= m ? most_arrivals / kTile : 0);
     if (std::min(runs, span) > kFarRuns) b |= 1u << (l - 2);
   }
   return b;
