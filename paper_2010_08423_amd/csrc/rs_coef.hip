@@ -1222,7 +1222,8 @@ __host__ __device__ inline uint32_t mul_lds(uint32_t k, uint32_t c_in, uint32_t 
 // runs that costs less than the launch (10^6-edge path query, 8 entries per
 // run: 3 us per level against 5), for long ones the blocks wait (4*10^6-edge
 // motif query, level 6: 224 us with the carry in the block, 190 without).
-template <class A, bool CARRIED>
+// FAR: some query of the launch has prefix sums of the tails.
+template <class A, bool CARRIED, bool FAR>
 __global__ __launch_bounds__(256) void k_coef_mul(A arg, uint32_t l, uint32_t wave_lds) {
   extern __shared__ uint64_t dyn_lds[];  // [4][wave_lds] then the carry
   const CoefQuery Q = arg.get(blockIdx.z);
@@ -1248,7 +1249,7 @@ __global__ __launch_bounds__(256) void k_coef_mul(A arg, uint32_t l, uint32_t wa
   const uint8_t* store = Q.store + y * flag_stride(Q.words);
   if constexpr (CARRIED) {
     const uint32_t units = (R.n + 3) / 4, waves = gridDim.x * 4;
-    const uint64_t* carry = carries(Q, l);
+    const uint64_t* carry = FAR ? carries(Q, l) : Q.carry;
     for (uint32_t u = blockIdx.x * 4 + wv; u < units; u += waves) {
       uint32_t flags = as_const((const uint32_t*)store)[u];
       if (!flags) continue;
@@ -1261,7 +1262,7 @@ __global__ __launch_bounds__(256) void k_coef_mul(A arg, uint32_t l, uint32_t wa
     }
   } else {
     uint64_t* carry = dyn_lds + 4 * (wave_lds / 8);
-    const bool far = (Q.far >> (l - 2)) & 1u;
+    const bool far = FAR && ((Q.far >> (l - 2)) & 1u);
     for (uint32_t run = blockIdx.x; run < R.runs; run += gridDim.x) {
       const uint32_t p_begin = R.tile(run) * kTile, p_end = min(R.tile(run + 1) * kTile, R.n);
       const uint32_t oe = open_part(Q.restart + y * flag_stride(Q.words), p_begin, p_end, lane);
@@ -1830,6 +1831,18 @@ static hipError_t launch_coef_lists(const A& a, const CoefGrid& g, hipStream_t s
   return hipGetLastError();
 }
 
+template <class A, bool FAR>
+static void launch_coef_mul(const A& a, const CoefGrid& g, uint32_t l, hipStream_t st) {
+  const uint32_t i = l - 1, nq = g.queries;
+  if (g.carry_mul[i]) {
+    hipLaunchKernelGGL(k_coef_carry<A>, dim3((g.runs[i] + 3) / 4, g.cblocks[i], nq), dim3(256), 0, st, a, l);
+    hipLaunchKernelGGL((k_coef_mul<A, true, FAR>), dim3(g.carry_mul[i], 1, nq), dim3(256), 4 * g.carry_lds[i], st, a, l,
+                       g.carry_lds[i]);
+  }
+  if (g.mul[i])  // the carry lies behind the waves' rows: at most one row
+    hipLaunchKernelGGL((k_coef_mul<A, false, FAR>), dim3(g.mul[i], 1, nq), dim3(256), 5 * g.lds[i], st, a, l, g.lds[i]);
+}
+
 template <class A>
 static hipError_t launch_coef_level(const A& a, const CoefGrid& g, uint32_t l, hipStream_t st) {
   const uint32_t i = l - 1, nq = g.queries;
@@ -1837,14 +1850,10 @@ static hipError_t launch_coef_level(const A& a, const CoefGrid& g, uint32_t l, h
   if ((g.far >> (l - 2)) & 1u) {
     hipLaunchKernelGGL(k_coef_fold<A>, dim3((g.runs[i] + 63) / 64, g.cblocks[i], nq), dim3(1024), 0, st, a, l);
     hipLaunchKernelGGL(k_coef_prefix<A>, dim3((g.runs[i] + 63) / 64, g.cblocks[i], nq), dim3(1024), 0, st, a, l);
+    launch_coef_mul<A, true>(a, g, l, st);
+  } else {
+    launch_coef_mul<A, false>(a, g, l, st);
   }
-  if (g.carry_mul[i]) {
-    hipLaunchKernelGGL(k_coef_carry<A>, dim3((g.runs[i] + 3) / 4, g.cblocks[i], nq), dim3(256), 0, st, a, l);
-    hipLaunchKernelGGL((k_coef_mul<A, true>), dim3(g.carry_mul[i], 1, nq), dim3(256), 4 * g.carry_lds[i], st, a, l,
-                       g.carry_lds[i]);
-  }
-  if (g.mul[i])  // the carry lies behind the waves' rows: at most one row
-    hipLaunchKernelGGL((k_coef_mul<A, false>), dim3(g.mul[i], 1, nq), dim3(256), 5 * g.lds[i], st, a, l, g.lds[i]);
   return hipGetLastError();
 }
 
