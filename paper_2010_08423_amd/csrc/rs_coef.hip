@@ -1627,10 +1627,12 @@ constexpr uint32_t kScanWaves = 4096;
 constexpr uint32_t kTopBlocks = 1024;
 // Blocks of the row products that go over a list in turn.
 constexpr uint32_t kMulBlocks = 2048;
-// Edges from which a thread of the backward pass takes four. (k = 8, Chung-Lu and
+// Edges, over the grid slices of a launch, from which a thread of the backward pass
+// takes four. (k = 8, Chung-Lu and
 // uniform graphs, one edge per thread against four, us per query: 6*10^5 edges 282
 // and 297, 219 and 231; 10^6 365 and 373, 237 and 241; 2*10^6 628 and 609, 354 and 336;
-// 4*10^6 1076 and 1046, 545 and 508.)
+// 4*10^6 1076 and 1046, 545 and 508. 24 queries on 10^6
+// edges: 5725 and 5506; one on 10^6 edges and 199 on 300: 3156 and 2411.)
 constexpr uint64_t kWideSets = 1400000;
 // Entries per run from which the carries get a launch of their own.
 constexpr uint64_t kLongRun = 32;
@@ -1716,9 +1718,10 @@ static uint64_t carve_setup(CoefQuery& q, const CoefShades& sh, uint8_t* base) {
   c.take(q.l_e, q.lstride);
   c.take(q.tail, tails);
   c.take(q.carry, tails);
-  c.take(q.started, 4 * kScanWaves);
-  c.take(q.open_end, 4 * kScanWaves);
-  c.take(q.seg, 4 * kScanWaves);
+  const uint64_t runs = std::min<uint64_t>(4 * kScanWaves, (q.m + kTile - 1) / kTile);  // (a run has a tile at least)
+  c.take(q.started, runs);
+  c.take(q.open_end, runs);
+  c.take(q.seg, runs);
   c.take(q.group, tails / 64 + width);
   return c.off;
 }
@@ -1762,7 +1765,7 @@ static uint32_t far_levels(const CoefQuery& q, const CoefShades& sh, const uint3
 // Grid sizes of the launches over one or more queries: the largest any needs.
 struct CoefGrid {
   uint32_t queries = 0, begin = 1, blocks = 1, k_max = 0, fwd_max = 0, fwd_min = 16, carried = 0, far = 0;
-  bool wide = false, small = true;
+  bool small = true;
   uint32_t runs[kCoefMaxK] = {}, waves[kCoefMaxK] = {}, cblocks[kCoefMaxK] = {}, mul[kCoefMaxK] = {}, carry_mul[kCoefMaxK] = {},
            lds[kCoefMaxK] = {}, carry_lds[kCoefMaxK] = {}, top = 1, per_wave = 64;
   uint64_t last = 0;  // last-level entries, over the queries and the largest
@@ -1774,7 +1777,6 @@ struct CoefGrid {
     k_max = std::max(k_max, q.k);
     fwd_max = std::max(fwd_max, q.fwd);
     fwd_min = std::min(fwd_min, q.plain && q.fwd > 3 ? 4u : 3u);
-    wide = wide || q.m >= kWideSets;
     small = small && q.words <= kSmallWords;
   }
   void levels(const CoefQuery& q, const CoefShades& sh, const uint32_t* cnt) {
@@ -1816,7 +1818,7 @@ static hipError_t launch_coef_sets(const A& a, const CoefGrid& g, hipStream_t st
   for (uint32_t l = g.fwd_min; l <= g.fwd_max; ++l)
     hipLaunchKernelGGL(k_coef_fwd<A>, dim3(g.blocks, nq), dim3(1024), 0, st, a, l);
   for (uint32_t d = 1; d + 2 <= g.k_max; ++d) {
-    if (g.wide)
+    if ((uint64_t)g.blocks * nq * kSetBlock >= kWideSets)
       hipLaunchKernelGGL((k_coef_bwd<A, 4>), dim3(g.blocks / 4, nq), dim3(1024), 0, st, a, d);
     else
       hipLaunchKernelGGL((k_coef_bwd<A, 1>), dim3(g.blocks, nq), dim3(1024), 0, st, a, d);
