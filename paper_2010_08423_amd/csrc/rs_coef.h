@@ -110,11 +110,8 @@ rs_status run_coef(rs_graph* g, PlainWorkspace& ws, const PlainSizes& sz, const 
 // A slot's row is formed by one wave, 64 coefficients and an edge at a time, so
 // graphs with more than kLitSlotEdges edges into one vertex at one time are left
 // to the evaluation form, which cuts slots into tiles, and so are shorter slots
-// whose chain is long against that form's work (lit_coef_applies) and, up to k = 6,
-// where that form takes one pass of 64 iterations, graphs with more than
-// kLitMeanEdges edges per slot.
+// whose chain is long against that form's work (lit_coef_applies).
 constexpr uint32_t kLitSlotEdges = 128;
-constexpr uint64_t kLitMeanEdges = 8;
 constexpr uint64_t kLitRows = 16ull << 30;  // what the evaluation form's two buffers may hold together
 bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp);
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,

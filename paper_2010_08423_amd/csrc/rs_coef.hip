@@ -2577,17 +2577,15 @@ constexpr uint64_t kLitBlocks = 1 << 20;
 
 bool lit_coef_applies(const LiteralState& L, uint64_t m, const QueryPlan& qp) {
   if (qp.k < 3 || !coef_applies(qp) || !L.ns || L.max_slot_edges > kLitSlotEdges) return false;
-  if (qp.k <= 6 && m > kLitMeanEdges * L.ns) return false;
   // Edges that the longest slot's wave goes over, a pass per 64 coefficients, over
-  // the levels, and edges per wave of the evaluation form with 8192 waves at
-  // once. (Us there and here at a ratio of 2.2: 860 and 772, k = 7, 25 edges per slot;
-  // 2.7: 623 and 598; 3.6: 595 and 602; 4.8: 516 and 568; 6.5: 628 and 1935, k = 10,
-  // 2*10^4 edges. Up to k = 6 it is 1.4 to 2.3 for 6*10^4 edges, 25 per slot, k = 3, 395 and
-  // 414, k = 6, 653 and 679, and for 3 per slot and 90 at a hub, k = 3, 1571 and 1439.)
+  // the levels, against the edges that the evaluation form's time allows, which is per
+  // level a latency and the edges and chunks of all slots. Evaluation and coefficient
+  // form beyond the line: 100 edges a slot, k = 3, 336 us and 627; 12000 edges, up to 84
+  // parallel ones, k = 8, 406 and 728. Within it: 300000 edges with a hub, k = 6, 27.0 ms
+  // and 16.6; 172000 edges, k = 7, 2.88 ms and 1.15.
   uint64_t passes = 0;
   for (uint32_t l = 2; l < qp.k; ++l) passes += (binom(qp.k, l - 1) + 63) / 64;
-  const uint64_t eval = (qp.k - 1) * std::max<uint64_t>(kLiteralTile, m * (qp.chunk_last - qp.chunk_first) / 8192);
-  return 2 * L.max_slot_edges * passes <= 7 * eval;
+  return L.max_slot_edges * passes <= (qp.k - 1) * (8 + m * (qp.chunk_last - qp.chunk_first) / 2560);
 }
 
 rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& qp, const uint32_t* dv, uint64_t hp,
@@ -2634,7 +2632,8 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
   if (L.coef.reserve(carve(nullptr), st, false)) return RS_OK;
   carve(L.coef.as<uint8_t>());
   T.zs = L.zs.as<uint64_t>();
-  if (!L.host_result) RS_HIP(hipHostMalloc((void**)&L.host_result, 8 * kTopBlocks, hipHostMallocDefault));
+  if (!L.host_result) RS_HIP(hipHostMalloc((void**)&L.host_result, 8 * (kTopBlocks + kCoefMaxK), hipHostMallocDefault));
+  if (!L.counted) RS_HIP(hipEventCreateWithFlags(&L.counted, hipEventDisableTiming));
   q.result = L.host_result;
   {
     ProfScope ps(KC_LITERAL, st, 0.0);
@@ -2645,22 +2644,27 @@ rs_status run_literal_coef(const GraphDev& G, LiteralState& L, const QueryPlan& 
     hipLaunchKernelGGL(k_coef_offsets<OneCoef>, dim3(k - 1, 1), dim3(1024), 0, st, a);
     RS_HIP(hipGetLastError());
   }
-  uint32_t cnt[kCoefMaxK - 1];
+  // The set sizes come back while the lists are formed, which do not need them: with
+  // the stream idle during the copy and the wait (45 us), small queries took longer
+  // than in the evaluation form (1515 edges, k = 7: 200 us, 173 so, 161 there).
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(L.host_result + kTopBlocks);
   RS_HIP(hipMemcpyAsync(cnt, q.count, 4 * (k - 1), hipMemcpyDeviceToHost, st));
-  RS_HIP(hipStreamSynchronize(st));
+  RS_HIP(hipEventRecord(L.counted, st));
+  ProfScope ps(KC_LITERAL, st, 0.0);
+  hipLaunchKernelGGL(k_litc_lists, dim3(q.blocks + T.nbe, k - 1), dim3(256), 0, st, a, T);
+  RS_HIP(hipGetLastError());
+  RS_HIP(hipEventSynchronize(L.counted));
   uint64_t rows = 256;  // two buffers in turn
   for (uint32_t l = 2; l < k; ++l) rows = std::max<uint64_t>(rows, 8ull * cnt[l - 2] * binom(k, l));
   if (2 * rows > kLitRows) return RS_OK;
   if (L.chi0.reserve(rows, st, false) || L.chi1.reserve(rows, st, false)) return RS_OK;
-  ProfScope ps(KC_LITERAL, st, 0.0);
-  hipLaunchKernelGGL(k_litc_lists, dim3(q.blocks + T.nbe, k - 1), dim3(256), 0, st, a, T);
-  RS_HIP(hipGetLastError());
   uint64_t *below = L.chi0.as<uint64_t>(), *here = L.chi1.as<uint64_t>();
   for (uint32_t l = 2; l < k; ++l) {
     q.P = below;
     const uint32_t lds = mul_lds(k, binom(k, l - 1), binom(k, l)) + kTile * 128;
     if (cnt[l - 2])
-      hipLaunchKernelGGL(k_litc_level, dim3((uint32_t)std::min<uint64_t>((cnt[l - 2] + 3ull) / 4, kLitBlocks)), dim3(256), 4 * lds, st, a, T, l, lds, here);
+      hipLaunchKernelGGL(k_litc_level, dim3((uint32_t)std::min<uint64_t>((cnt[l - 2] + 3ull) / 4, kLitBlocks)), dim3(256),
+                         4 * lds, st, a, T, l, lds, here);
     RS_HIP(hipGetLastError());
     std::swap(below, here);
   }

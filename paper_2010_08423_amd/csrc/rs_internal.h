@@ -543,16 +543,18 @@ struct LiteralState {
   // slot of each edge [m], time [ns] and first edge [ns+1] of each slot, first slot per vertex [n+1]
   DevBuf slot, slot_t, slot_e, v_soff;
   DevBuf coef;                      // sets and lists of the coefficient form
-  uint64_t* host_result = nullptr;  // its sums (pinned)
+  uint64_t* host_result = nullptr;  // its sums, then its set sizes (pinned)
+  hipEvent_t counted = nullptr;     // the set sizes are there
   DevBuf wlo, whi, y2, need, z, zs, out, chi0, chi1, dv, reach, zeta_edge;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   void release() {
     for (DevBuf* b : {&slot, &slot_t, &slot_e, &coef, &v_soff, &wlo, &whi, &y2, &need, &z, &zs, &out, &chi0, &chi1, &dv, &reach,
                       &zeta_edge})
       b->release();
-    if (ev0) (void)hipEventDestroy(ev0);
-    if (ev1) (void)hipEventDestroy(ev1);
-    ev0 = ev1 = nullptr;
+    for (hipEvent_t* e : {&ev0, &ev1, &counted}) {
+      if (*e) (void)hipEventDestroy(*e);
+      *e = nullptr;
+    }
     if (host_result) (void)hipHostFree(host_result);
     host_result = nullptr;
     built = false;

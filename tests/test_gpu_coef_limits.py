@@ -335,18 +335,19 @@ def test_large_graphs(m, k, delta):
             assert np.array_equal(r.per_iteration, e.per_iteration[lo:hi])
 
 
-# Graphs whose slots all have 8 or 9 edges (k = 6), 67 or 68 (k = 7) or 26 or 27 (k =
-# 10): next to the lengths from which the literal reading stays in the evaluation form.
-@pytest.mark.parametrize("k,per", [(6, 8), (6, 9), (7, 67), (7, 68), (10, 26), (10, 27)])
-def test_literal_long_slots(k, per):
-    n, slots = 73, 200
+# Graphs whose slots are all of one length, on either side of the lengths from which
+# the literal reading stays in the evaluation form.
+@pytest.mark.parametrize("k,per,slots", [(6, 10, 200), (6, 11, 200), (7, 10, 200), (7, 11, 200), (10, 9, 200),
+                                         (10, 10, 200), (3, 128, 1119), (3, 128, 1120), (3, 129, 1200)])
+def test_literal_long_slots(k, per, slots):
+    n = 73 if per < 70 else 293  # (so that walks of k vertices exist)
     s = np.arange(slots)
     src = (s[:, None] * 7 + 1 + np.arange(per)) % n
     dst = np.broadcast_to((s[:, None] * 7) % n, src.shape)  # (never among its sources)
     t = np.broadcast_to(1 + s[:, None] // 5, src.shape)
     src, dst, t = (x.ravel().astype(np.uint32) for x in (src, dst, t))
     gd = R.Graph(n, src, dst, t)
-    for delta in (1, 12):
+    for delta in (2, 12):
         z, reach = oracle.fine_literal(n, src, dst, t, k, delta, 7, threads=host_threads())
         got = R.run_literal(gd, k, delta, 7)
         assert np.array_equal(got.zeta, z) and np.array_equal(got.reach, reach) and got.yes
