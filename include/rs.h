@@ -336,15 +336,16 @@ rs_status rs_run_noalloc(const rs_graph* g, const rs_query* q, uint64_t* per_ite
  * sizes. Parts of a range, k = 2, k > 12, queries whose rows alone exceed that
  * memory, and every query of a call with tuning run in the evaluation form:
  *
- * Every (query, 64-iteration chunk) is a unit
- * with its own prefix-state buffers; units are packed into rounds, and four
- * stream lanes run one round each at a time. A round holds at most max_slots
- * units and at most a quarter of the HBM budget (a third of free device
- * memory) in prefix state, and never more than 20 GiB, so the lanes together
- * stay within the budget. A round runs level l of all its units in shared launches (one per product-row
- * width), each walking a device table of unit descriptors. The launch
- * sequence is captured once per batch shape into a hipGraph and replayed with
- * new descriptors (tune->no_graph = 1 enqueues it directly).
+ * Every (query, 64-iteration chunk) is a unit with its own prefix-state
+ * buffers; units are packed into rounds, and four stream lanes run one round
+ * each at a time. A round holds at most max_slots units and at most a quarter of
+ * the HBM budget (a third of free device memory) in prefix state, and never more
+ * than 20 GiB, so the lanes together stay within the budget. A round runs level
+ * l of all its units in shared launches (one per product-row width), each
+ * walking a device table of unit descriptors. The launch sequence is captured
+ * once per batch shape into a hipGraph and replayed with new descriptors
+ * (tune->no_graph = 1 enqueues it directly).
+ *
  * results[i].status holds each query's status (RS_EINVAL for an invalid
  * query, which is skipped); the call returns the first error, or RS_OK. Where
  * a part of the batch fails as a whole, that error is returned, and queries whose
