@@ -10,6 +10,7 @@
 // 3.8 million last-level entries have 2.1 million distinct windows.)
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
+#include <type_traits>
 
 #include "rs_internal.h"
 
@@ -82,33 +83,37 @@ uint64_t group_temp_bytes(uint64_t m, uint64_t n) {
   return std::max<uint64_t>(a, b) + 256;
 }
 
-uint64_t group_bytes(uint64_t m, uint64_t n, uint32_t kq) {
+// The parts of a buffer at `buf`, 256-byte aligned, and the offset of their end.
+static uint64_t carve(uint8_t* buf, uint64_t m, uint32_t kq, GroupView& v) {
   const uint64_t e = m + kEdgePad;
-  // keys in/out, indices in/out, heads/gid, starts, ghi, glo, rows, count, sort temp
-  return 8 * e * 2 + 4 * e * 2 + 4 * e * 2 + 4 * (e + 1) + 4 * e * 2 + 8 * e * kq + 256 + group_temp_bytes(m, n);
+  uint64_t off = 0;
+  auto take = [&](auto*& p, uint64_t count) {
+    p = reinterpret_cast<std::remove_reference_t<decltype(p)>>((uintptr_t)buf + off);
+    off += (sizeof(*p) * count + 255) & ~255ull;
+  };
+  take(v.key_in, e);
+  take(v.key_out, e);
+  take(v.idx_in, e);
+  take(v.idx_out, e);
+  take(v.head, e);
+  take(v.gid, e);
+  take(v.gstart, e + 1);
+  take(v.ghi, e);
+  take(v.glo, e);
+  take(v.gq, e * kq);
+  take(v.gcount, 1);
+  take(v.temp, 0);
+  return off;
+}
+
+uint64_t group_bytes(uint64_t m, uint64_t n, uint32_t kq) {
+  GroupView v;
+  return carve(nullptr, m, kq, v) + group_temp_bytes(m, n);
 }
 
 GroupView group_view(uint8_t* buf, uint64_t m, uint32_t kq) {
-  const uint64_t e = m + kEdgePad;
   GroupView v;
-  uint8_t* p = buf;
-  auto take = [&](uint64_t bytes) {
-    uint8_t* r = p;
-    p += (bytes + 255) & ~255ull;
-    return r;
-  };
-  v.key_in = (uint64_t*)take(8 * e);
-  v.key_out = (uint64_t*)take(8 * e);
-  v.idx_in = (uint32_t*)take(4 * e);
-  v.idx_out = (uint32_t*)take(4 * e);
-  v.head = (uint32_t*)take(4 * e);
-  v.gid = (uint32_t*)take(4 * e);
-  v.gstart = (uint32_t*)take(4 * (e + 1));
-  v.ghi = (uint32_t*)take(4 * e);
-  v.glo = (uint32_t*)take(4 * e);
-  v.gq = (uint64_t*)take(8 * e * kq);
-  v.gcount = (uint32_t*)take(256);
-  v.temp = p;
+  carve(buf, m, kq, v);
   return v;
 }
 
