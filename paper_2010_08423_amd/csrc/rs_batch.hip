@@ -585,8 +585,12 @@ rs_status batch_plan(const rs_graph* const* graphs, const rs_query* queries, uin
     P.qs.push_back(Q);
     P.qidx.push_back(i);
     qgraph.push_back(g);
-    key += "|" + std::to_string((uintptr_t)g) + ":" + std::to_string(n) + ":" + std::to_string(m) + ":" +
-           std::to_string(qp.k) + ":" + std::to_string(qp.chunk_first) + "-" + std::to_string(qp.chunk_last);
+    key += "|" + std::to_string(n) + ":" + std::to_string(m) + ":" + std::to_string(qp.k) + ":" +
+           std::to_string(qp.chunk_first) + "-" + std::to_string(qp.chunk_last);
+    // the arrays that captured launches hold pointers to (a later graph may lie at a destroyed one's handle)
+    for (const void* p : {(const void*)Q.e_src, (const void*)Q.e_dst, (const void*)Q.e_t, (const void*)Q.e_out,
+                          (const void*)Q.hi, (const void*)Q.in_off})
+      key += "," + std::to_string((uintptr_t)p);
     for (uint64_t c = qp.chunk_first; c < qp.chunk_last; ++c) chunks.push_back(Chunk{qslot, c * kLanes});
   }
   P.per_query_bytes = pq_off;

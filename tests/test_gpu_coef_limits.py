@@ -1,6 +1,8 @@
 """GPU parity of the coefficient form where a size or a launch reaches a limit:
 look-ups far past a block of edges, launches of more work items than one
 dimension of a grid takes, outputs cut into parts, and batches cut into rounds."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -351,3 +353,29 @@ def test_literal_long_slots(k, per, slots):
         z, reach = oracle.fine_literal(n, src, dst, t, k, delta, 7, threads=host_threads())
         got = R.run_literal(gd, k, delta, 7)
         assert np.array_equal(got.zeta, z) and np.array_equal(got.reach, reach) and got.yes
+
+
+# A captured batch holds pointers to its graphs' arrays: a graph that takes a destroyed
+# one's handle and sizes, but not its memory, is not run with them.
+def test_batch_after_graph_is_replaced():
+    hip = ctypes.CDLL("libamdhip64.so")
+    n, k = 500, 6
+    g = inputs.uniform_graph(n, 20000, 60, seed=1)
+    held = []
+    for i in range(4):
+        name = np.random.default_rng(i).permutation(n).astype(np.uint32)  # (so all graphs have as many edges)
+        src, dst = name[g.src], name[g.dst]
+        z, reach, F = oracle.fine_grained(n, src, dst, g.t, k, 4, 9 + i, threads=host_threads())
+        gd = R.Graph(n, src, dst, g.t)
+        for _ in range(2):
+            parts = [inputs.Query(k=k, delta=4, seed=9 + i, it_begin=a, it_end=b) for a, b in ((0, 20), (20, 64))]
+            r, s = R.run_batch([gd] * 2, parts)
+            assert s == 0 and r[0].fingerprint ^ r[1].fingerprint == F
+        size = 4 * gd.info()["m"]
+        gd.close()
+        for _ in range(8):
+            p = ctypes.c_void_p()
+            assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(size)) == 0
+            held.append(p)
+    for p in held:
+        assert hip.hipFree(p) == 0
